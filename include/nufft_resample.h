@@ -78,7 +78,9 @@ typedef enum {
 } nr_precision;
 
 typedef enum {
-    NR_METHOD_AUTO = 0,   /* per instance: NR_METHOD_CELLRUN when its time series spends
+    NR_METHOD_AUTO = 0,   /* band-limited nodes where the plan's templates share segments
+                             (nr_node_info); otherwise per instance
+                             NR_METHOD_CELLRUN when its time series spends
                              at least 24 samples (12 in plans of 4096 or more
                              instances) in each grid cell it visits or its
                              spreader workgroup needs at most 1/5 of a compute unit's
@@ -208,9 +210,27 @@ typedef struct {
     int64_t fallback_points; /* samples of instances using the log1p/expm1 form of tau */
 } nr_class_info;
 
+/*
+ * The band-limited nodes of a kernel class.  Under NR_METHOD_AUTO (real
+ * strain, sigma 2, parts, flush_period, moment_mode, epilogue and tune left 0)
+ * a plan whose templates share segments may resample each instance from node
+ * values instead of its samples: the segment, filtered to the few hertz around
+ * a reference frequency at a rate of a few times that width, once for all
+ * templates of that frequency.  The sum over the nodes equals the sum over the
+ * samples to 3e-8 (FP32 classes) or 1e-11 (FP64), below the class's kernel
+ * error.  Such a class reports method NR_METHOD_CELLRUN and parts 1.
+ */
+typedef struct {
+    int32_t width;       /* spreading width on the nodes; 0: the class reads samples, all else 0 */
+    int32_t degree;      /* degree of its kernel pieces in the per-cell position */
+    int64_t nodes;       /* sum over the class's instances of their nodes */
+    int64_t values;      /* node values that the plan's filter writes for the class's precision */
+    int64_t filter_macs; /* real multiply-adds of that filter per call */
+} nr_node_info;
+
 /* Kernel time per stage, accumulated over launches since the last read. */
 typedef enum {
-    NR_STAGE_LAYOUT = 0,   /* lane-major strain copy */
+    NR_STAGE_LAYOUT = 0,   /* lane-major strain copy, node filter */
     NR_STAGE_TAU = 1,      /* point stream (staged method) */
     NR_STAGE_SPREAD = 2,   /* spreading (fused method: tau + spreading) */
     NR_STAGE_EPILOGUE = 3, /* FFT, deconvolution, power / segment sum, invalid fill */
@@ -313,6 +333,9 @@ nr_status nufft_resample_query(nr_plan p, nr_plan_info* info);
 
 /* Description of kernel class c, 0 <= c < n_classes. */
 nr_status nufft_resample_query_class(nr_plan p, int32_t c, nr_class_info* info);
+
+/* Band-limited nodes of kernel class c, 0 <= c < n_classes. */
+nr_status nufft_resample_query_nodes(nr_plan p, int32_t c, nr_node_info* info);
 
 /* Host array [n_inst + 1] of bin offsets into spectra / power. */
 nr_status nufft_resample_bin_offsets(nr_plan p, int64_t* offsets);

@@ -44,6 +44,11 @@ struct InstDev {
     int32_t ndeg;       // tau: 0 identity; > 0 Horner degree in the sample index; < 0 log1p/expm1
     int32_t coef_off;   // first Horner coefficient of this instance
     int32_t entry;      // position in the class's template-major instance list
+    int32_t nodes;      // node classes: nodes of the instance (else 0).  There strain_off is the
+                        // first node value, C the samples between nodes, the low half of pt_off
+                        // the sample position of the first node (negative: the filter reaches
+                        // before sample 0) and its high half one less than the nodes that
+                        // are at least a cell apart
 };
 
 // One segment of a class: where its samples are and where its lane-major copy goes.
@@ -139,6 +144,70 @@ struct EpilogueOut {
     int32_t out_fp64;        // outputs and rows are double (else float)
 };
 
+// Node classes (nr_nodes.hpp).
+constexpr int kNodeTile = 64;      // nodes of one filter workgroup
+constexpr int kFilterRows = 16;    // reference frequencies of one filter tile
+constexpr int kNodeBatch = 16;     // instances of one small-grid spreader workgroup
+constexpr int kNodeDftMax = 128;   // largest grid transformed by the small DFT
+
+// Row of accumulator i of the lanes l / 16 = g in a 16 x 16 matrix product.
+__host__ __device__ inline int mfma_row(bool fp64, int g, int i) { return fp64 ? 4 * i + g : 4 * g + i; }
+
+// Images of the filter's window folded onto one period of the carriers, by
+// precision (odd; the window's half-width is at most (images / 2 + 1/2) periods).
+constexpr int kImages32 = 5, kImages64 = 9;
+constexpr int kFilterTiles = 2;    // tiles of one filter workgroup at most
+
+// Work of one filter workgroup: nodes node0 .. node0 + 63 of one segment for
+// `tiles` consecutive tiles of 16 reference frequencies.
+struct FilterItem {
+    int64_t src_off;    // first sample of the segment in the caller's strain
+    int64_t z_off;      // node values of the first frequency ([16 tiles][nodes])
+    int64_t tap_off;    // carriers of the first tile: per tile [4 ksteps][64 lanes] (cosine, -sine) pairs
+    int64_t win_off;    // window [16 ksteps][images, padded to four]
+    int32_t L;          // samples
+    int32_t D;          // samples between nodes
+    int32_t Q;          // period of the carriers in samples
+    int32_t ksteps;     // sixteenths of the Q / 2 + 1 folded samples, rounded up
+    int32_t tiles;
+    int32_t nodes;      // nodes of the segment
+    int32_t node0;
+    int32_t j0;         // sample position of node 0
+};
+
+// Arguments of the node spreader for one class.
+struct NodeArgs {
+    const InstDev* inst;
+    const double* coef;      // tau series
+    const void* poly;        // per tap pair the even, then the odd coefficients of the kernel
+    const void* z;           // node values
+    const void* dft;         // small grids: [mtiles][ksteps][64] DFT rows with the deconvolution
+    const void* dec;         // large grids: deconvolution, twiddles and FFT plan
+    const void* twiddle;
+    FftPlanDev fft;
+    int64_t count;
+    int64_t row_base;
+    int32_t n;
+    int32_t w;
+    int32_t kmax;
+    int32_t m0max;           // kmax / 2: row q of the DFT is mode q - m0max
+    int32_t mtiles;          // 0: large grid
+    int32_t ksteps;
+    int32_t strip;           // unwrapped cells of one wave's strip
+    int32_t gstride;         // small grids: values of one instance's strip and grid
+    int32_t im_off;          // small grids: first imaginary part after the first real part
+};
+
+// LDS of a large-grid workgroup: the grid, and four strips or the FFT's other half.
+inline size_t node_fft_lds_bytes(int fp64, int n, int strip)
+{
+    return (size_t)(n + (4 * strip > n ? 4 * strip : n)) * (fp64 ? 16 : 8);
+}
+size_t filter_lds_bytes(int fp64, int D, int Q, int ksteps, int images);
+hipError_t launch_node_filter(const FilterItem* items, int64_t count, size_t lds, const void* carriers,
+                              const void* window, const void* strain, void* z, int strain_fp64, int fp64,
+                              hipStream_t st);
+
 // Launch wrappers (defined in nr_kernels.hip).
 // max_entries: the largest parts * C * 64 of the segments (sizes the grid).
 hipError_t launch_strain_lane_major(const SegDev* segs, int32_t n_segs, int64_t max_entries, const void* strain,
@@ -165,6 +234,7 @@ struct EpilogueTable {
 hipError_t launch_epilogue_multi(const EpilogueTable& t, int64_t blocks, int sum_mode, EpilogueOut out, int fp64,
                                  int out_fp64, size_t lds, hipStream_t st);
 int64_t epilogue_blocks(const EpilogueArgs& a, int sum_mode);
+hipError_t launch_node_spread(const NodeArgs& a, int fp64, const EpilogueOut& o, hipStream_t st);
 hipError_t launch_tau(const SpreadArgs& a, int fp64, hipStream_t st);
 // The direct non-uniform DFT baseline: mode 0 writes spectra/power at the
 // instances' bin offsets, mode 1 power rows for the two-pass segment sum.

@@ -1,0 +1,629 @@
+// Band-limited nodes: the resampling sum over a segment's samples replaced by
+// the same sum over far fewer points.
+//
+// The sum of an instance is X_m = sum_j x_j E_m(j), E_m(j) = exp(-2 pi i f_m
+// dtau_j).  As a function of the sample index every E_m is a slow function
+// times the carrier exp(-2 pi i f_ref j / fs): its local frequency f_m dtau'
+// stays within a few hertz of f_ref.  A function of band half-width P is
+// fixed by its values at nodes j_b = D b taken at a rate fs / D above 2 P,
+//   E_m(j) exp(+2 pi i f_ref j / fs) = sum_b E_m(j_b) exp(+2 pi i f_ref j_b / fs) h((j - j_b) / D)
+// with the interpolation kernel h (a Kaiser-windowed sinc of half-width H
+// nodes: band-limited interpolation, the polyphase form of Crochiere and
+// Rabiner), so that
+//   X_m = sum_b z_b E_m(j_b),   z_b = sum_s x_{j_b + s} h(s / D) exp(-2 pi i f_ref s / fs).
+// The z_b depend on the segment and on f_ref only: every template of a
+// sub-band shares them, and an instance is a resampling sum over its nodes
+// (about 120 for a 30 s segment and a 1 Hz sub-band instead of 7680 samples),
+// the same type-I NUFFT (Sec. III.B, App. A) at the same tau.
+//
+//   node_filter    z of every (segment, f_ref, node), a short-time Fourier
+//                  transform of the segment on the matrix cores.
+//   node_spread    tau, heterodyne and ES spreading of an instance's nodes
+//                  onto its grid in LDS, then the transform of the grid to
+//                  the instance's modes (a small DFT on the matrix cores, or
+//                  the Stockham FFT for large grids), deconvolution, power.
+#pragma once
+
+#include "nr_fft.hpp"
+#include "nr_internal.hpp"
+
+namespace nr {
+
+// ------------------------------------------------------- matrix products --
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// 16 x 16 tile of C += A B over four values of the contraction index: lane l
+// gives A[m = l % 16][k = l / 16] and B[k = l / 16][n = l % 16]; accumulator
+// i of lane l is C[mfma_row<T>(l / 16, i)][n = l % 16].
+template <typename T>
+struct Mfma;
+template <>
+struct Mfma<float> {
+    using acc = f32x4;
+    static __device__ __forceinline__ acc step(float a, float b, acc c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+};
+template <>
+struct Mfma<double> {
+    using acc = f64x4;
+    static __device__ __forceinline__ acc step(double a, double b, acc c)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+};
+
+// ---------------------------------------------------------------- filter --
+
+// Reference frequencies are multiples of fs / Q, Q = kNodeRefs D, so the
+// carrier repeats every Q samples and z is a short-time Fourier transform:
+// the windowed samples around a node, folded modulo Q, times Q-point carriers
+// (the weighted overlap-add filter bank of Crochiere and Rabiner).  With the
+// window's symmetry and y(k) = sum_i h(k + Q i) x_{j_b + k + Q i},
+//   Re z_b = sum_{k <= Q/2} cos(2 pi r k / Q) (y(k) + y(-k))   (k = 0, Q/2 halved)
+//   Im z_b = -sum_{k <= Q/2} sin(2 pi r k / Q) (y(k) - y(-k)),
+// two matrix products A B over Q / 2 + 1 values: A = carriers [16 references
+// r of a tile][k], B = folded samples [k][16 nodes].
+//
+// One workgroup: 64 consecutive nodes (16 per wave) of one segment, MT tiles.
+// Node windows overlap, so the samples are staged in LDS once and each lane
+// folds the B values of its (k, node) itself, for all MT tiles: 2 I reads and
+// 4 I operations beside 2 MT matrix steps.  D = 4 (mod 8) spreads the lanes'
+// reads (node stride D, four consecutive k) over all banks.  In FP32 four chains
+// per product keep the rounding of the FP32 sums below that of the spreading.
+// Measured on the 1 h workload (120 segments of 7680 samples, 41 carriers at
+// 121 and 29 at 243 nodes): 44 us, against 106 us for a product of the
+// unfolded taps (1260 instead of 253 contraction steps per product).
+template <typename T, typename Ti, int MT, int I>
+__device__ __forceinline__ void node_filter_block(const FilterItem& it, const Ti* __restrict__ strain,
+                                                  const T* __restrict__ carriers, const T* __restrict__ window,
+                                                  cpx<T>* __restrict__ z, T* __restrict__ lds)
+{
+    constexpr int IS = (I + 3) / 4 * 4;       // stride of the window's images of one k
+    constexpr int R = I / 2;                  // images i = -R .. R
+    const int D = it.D, Q = it.Q, kp = 16 * it.ksteps, reach = R * Q + kp;
+    T* ws = lds;
+    T* xs = lds + kp * IS;
+    // window of the workgroup's nodes: sample w0 is xs[0]
+    const int64_t w0 = (int64_t)it.j0 + (int64_t)it.node0 * D - reach;
+    const int len = (kNodeTile - 1) * D + 2 * reach + 1;
+    const Ti* __restrict__ src = strain + it.src_off;
+    // eight loads in flight per thread
+    for (int q0 = threadIdx.x; q0 < len; q0 += 8 * kBlock) {
+        Ti v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t j = w0 + q0 + u * kBlock;
+            v[u] = q0 + u * kBlock < len && j >= 0 && j < it.L ? src[j] : Ti(0);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q0 + u * kBlock < len) xs[q0 + u * kBlock] = (T)v[u];
+    }
+    for (int q0 = threadIdx.x; q0 < kp * IS; q0 += 8 * kBlock) {
+        T v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = q0 + u * kBlock < kp * IS ? window[it.win_off + q0 + u * kBlock] : T(0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q0 + u * kBlock < kp * IS) ws[q0 + u * kBlock] = v[u];
+    }
+    __syncthreads();
+    const int wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int nn = lane & 15, kq = lane >> 4;
+    const int node = 16 * wave + nn;
+    const T* __restrict__ xp = xs + node * D + reach + kq;   // x at +k, -k of the node's centre
+    const T* __restrict__ xm = xs + node * D + reach - kq;
+    const T* __restrict__ wk = ws + kq * IS;
+    using V2 = cpx<T>;                                       // (cosine, -sine) of a lane
+    const V2* __restrict__ tp = reinterpret_cast<const V2*>(carriers) + it.tap_off + lane;
+    const int64_t tile = (int64_t)it.ksteps * 4 * 64;
+    constexpr int CH = sizeof(T) == 4 ? 4 : 1;                // chains
+    typename Mfma<T>::acc re[MT][CH], im[MT][CH];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int c = 0; c < CH; ++c) re[t][c] = im[t][c] = typename Mfma<T>::acc{};
+    V2 a[MT][4];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) a[t][c] = tp[t * tile + c * 64];
+    for (int ks = 0; ks < it.ksteps; ++ks) {
+        // the next step's carriers, in flight behind this step's products
+        V2 an[MT][4];
+        tp += ks + 1 < it.ksteps ? 256 : 0;
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) an[t][c] = tp[t * tile + c * 64];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            T e = T(0), o = T(0);
+#pragma unroll
+            for (int i = -R; i <= R; ++i) {
+                const T w = wk[4 * c * IS + i + R], p = xp[4 * c + i * Q], m = xm[-4 * c - i * Q];
+                e = fma(w, p + m, e);
+                o = fma(w, p - m, o);
+            }
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                re[t][c % CH] = Mfma<T>::step(a[t][c].x, e, re[t][c % CH]);
+                im[t][c % CH] = Mfma<T>::step(a[t][c].y, o, im[t][c % CH]);
+            }
+        }
+        xp += 16;
+        xm -= 16;
+        wk += 16 * IS;
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a[t][c] = an[t][c];
+    }
+    const int b = it.node0 + node;
+    if (b >= it.nodes) return;
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int f = kFilterRows * t + mfma_row(sizeof(T) == 8, kq, i);
+            T r = re[t][0][i], q = im[t][0][i];
+            if constexpr (CH == 4) {
+                r = (r + re[t][1][i]) + (re[t][2][i] + re[t][3][i]);
+                q = (q + im[t][1][i]) + (im[t][2][i] + im[t][3][i]);
+            }
+            z[it.z_off + (int64_t)f * it.nodes + b] = cpx<T>{r, q};
+        }
+}
+
+template <typename T, typename Ti, int I>
+__global__ __launch_bounds__(kBlock) void node_filter_kernel(const FilterItem* __restrict__ items,
+                                                             const Ti* __restrict__ strain,
+                                                             const T* __restrict__ carriers,
+                                                             const T* __restrict__ window, cpx<T>* __restrict__ z)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    T* lds = reinterpret_cast<T*>(smem_raw);
+    const FilterItem it = items[blockIdx.x];
+    if (uniform(it.tiles) == 1)
+        node_filter_block<T, Ti, 1, I>(it, strain, carriers, window, z, lds);
+    else
+        node_filter_block<T, Ti, kFilterTiles, I>(it, strain, carriers, window, z, lds);
+}
+
+// ---------------------------------------------------------------- spread --
+
+// Instance records and series are the same for a whole wave: read through the
+// constant address space they come over the scalar cache into scalar
+// registers (after an LDS fence the compiler would otherwise load them per
+// lane).
+#define NR_CONST __attribute__((address_space(4)))
+template <typename X>
+__device__ __forceinline__ const NR_CONST X* as_const(const X* p)
+{
+    return (const NR_CONST X*)(uintptr_t)p;
+}
+
+__device__ __forceinline__ InstDev load_inst(const InstDev* p)
+{
+    static_assert(sizeof(InstDev) == 96, "twelve words");
+    const NR_CONST uint64_t* q = (const NR_CONST uint64_t*)(uintptr_t)p;
+    uint64_t w[12];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) w[i] = q[i];
+    InstDev d;
+    __builtin_memcpy(&d, w, sizeof d);
+    return d;
+}
+
+// dtau at NP sample positions (series of dtau_of, uniform degree).
+template <int NP, int N>
+__device__ __forceinline__ void node_horner(const NR_CONST double* b, const double* x, double* out)
+{
+#pragma unroll
+    for (int e = 0; e < NP; ++e) out[e] = b[N - 1];
+#pragma unroll
+    for (int k = N - 2; k >= 0; --k) {
+#pragma unroll
+        for (int e = 0; e < NP; ++e) out[e] = fma(out[e], x[e], b[k]);
+    }
+#pragma unroll
+    for (int e = 0; e < NP; ++e) out[e] *= x[e];
+}
+
+template <int NP>
+__device__ __forceinline__ void node_dtau(int ndeg, double c, const NR_CONST double* b, const double* x,
+                                          double* out)
+{
+    switch (ndeg) {
+    case 0:
+#pragma unroll
+        for (int e = 0; e < NP; ++e) out[e] = x[e] * c;
+        return;
+#define NR_N(N) \
+    case N: node_horner<NP, N>(b, x, out); return;
+        NR_N(1) NR_N(2) NR_N(3) NR_N(4) NR_N(5) NR_N(6) NR_N(7) NR_N(8) NR_N(9) NR_N(10) NR_N(11) NR_N(12)
+#undef NR_N
+    default:
+        break;
+    }
+#pragma unroll
+    for (int e = 0; e < NP; ++e) out[e] = b[ndeg - 1];
+    for (int k = ndeg - 2; k >= 0; --k) {
+#pragma unroll
+        for (int e = 0; e < NP; ++e) out[e] = fma(out[e], x[e], b[k]);
+    }
+#pragma unroll
+    for (int e = 0; e < NP; ++e) out[e] *= x[e];
+}
+
+// exp(-2 pi i ph) applied to z, ph in cycles.
+__device__ __forceinline__ cpx<float> node_heterodyne(double ph, cpx<float> z)
+{
+    const float f = (float)(ph - rint(ph));
+    const float cs = __builtin_amdgcn_cosf(f), sn = __builtin_amdgcn_sinf(f);
+    return cpx<float>{z.x * cs + z.y * sn, z.y * cs - z.x * sn};
+}
+__device__ __forceinline__ cpx<double> node_heterodyne(double ph, cpx<double> z)
+{
+    double sn, cs;
+    sincospi(2.0 * (ph - rint(ph)), &sn, &cs);
+    return cpx<double>{z.x * cs + z.y * sn, z.y * cs - z.x * sn};
+}
+
+// Orders the LDS accesses of one wave's lanes among themselves (the hardware
+// runs them in program order; no instruction is emitted).
+__device__ __forceinline__ void lane_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Cells of a strip, real and imaginary part in one aligned word pair.
+template <typename T>
+struct Cell;
+template <>
+struct Cell<float> {
+    typedef float v __attribute__((ext_vector_type(2)));
+};
+template <>
+struct Cell<double> {
+    typedef double v __attribute__((ext_vector_type(2)));
+};
+
+// The W tap values of a node.  u = 1 - 2 frac(S) in (-1, 1]; tap t is
+// E_t(u^2) + u O_t(u^2) and, the kernel being even, tap W - 1 - t is E_t(u^2)
+// - u O_t(u^2): half the polynomial work.  poly: per pair t < W / 2 the NE
+// even coefficients, then the NE odd ones (W even).
+template <typename T, int W, int NE>
+__device__ __forceinline__ void node_taps(const NR_CONST T* poly, T u, T* a)
+{
+    const T u2 = u * u;
+#pragma unroll
+    for (int t = 0; t < W / 2; ++t) {
+        const NR_CONST T* pe = poly + t * 2 * NE;
+        T ev = pe[NE - 1], od = pe[2 * NE - 1];
+#pragma unroll
+        for (int k = NE - 2; k >= 0; --k) {
+            ev = fma(ev, u2, pe[k]);
+            od = fma(od, u2, pe[NE + k]);
+        }
+        a[t] = fma(u, od, ev);
+        a[W - 1 - t] = fma(-u, od, ev);
+    }
+}
+
+// The nodes [first, first + count) of an instance onto the wave's strip of
+// unwrapped cells; lane v takes nodes v * stride + r of them, r < stride.
+// Returns the unwrapped cell of the strip's first position.
+//
+// The lanes' nodes lie at least one cell apart, so within one tap no two
+// lanes meet and a plain read, add and write of the cell serves (an LDS
+// addition ds_add_f32 of 64 lanes took about 240 cycles here, four a lane);
+// the taps follow each other in program order.  Where consecutive nodes are
+// less than a cell apart (pair), a lane's two nodes share W + 1 cells and
+// their taps are summed in registers: 9 instead of 16 cell updates (W = 8).
+// 1 h workload, 122,501 instances of about 121 nodes: 1430 us per step with
+// LDS additions, 123 us with updates tap by tap, 94 us with the pairs (0.64 of
+// the VALU's issue, the rest the chain of updates); its sample spreader, the
+// cell-run kernel, takes 1240 us.
+template <typename T, int W, int NE>
+__device__ __forceinline__ int node_strip(const InstDev& d, const NodeArgs& a, int first, int count, int lane,
+                                          typename Cell<T>::v* strip)
+{
+    using V = typename Cell<T>::v;
+    const NR_CONST double* coef = as_const(a.coef + d.coef_off);
+    const cpx<T>* __restrict__ z = reinterpret_cast<const cpx<T>*>(a.z) + d.strain_off + first;
+    const NR_CONST T* poly = as_const(reinterpret_cast<const T*>(a.poly));
+    const double dfn = d.df * (double)a.n, hnn = 0.5 * (double)W;
+    const int j0 = (int)d.pt_off + first * d.C;
+    const int hi = (int)(d.pt_off >> 32);
+    const int apart = (hi & 0xffff) + 1;            // lanes' nodes at least a cell apart
+    const bool pair = (hi >> 16) != 0;
+    const int need = (count + kWave - 1) / kWave;
+    const int stride = need > apart ? need : apart;
+    int base = 0;
+    for (int r0 = 0; r0 < stride; r0 += 2) {
+        double x[2], dt[2];
+        cpx<T> zv[2];
+        bool on[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int b = lane * stride + r0 + e;
+            on[e] = r0 + e < stride && b < count;
+            const int bc = on[e] ? b : 0;
+            zv[e] = z[bc];
+            x[e] = (double)(j0 + bc * d.C);
+        }
+        node_dtau<2>(d.ndeg, d.c, coef, x, dt);
+        int g[2];
+        T u[2];
+        cpx<T> c[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const double S = fma(dfn, dt[e], -hnn), fl = floor(S);
+            g[e] = (int)fl;
+            u[e] = (T)fma(-2.0, S - fl, 1.0);
+            c[e] = node_heterodyne(d.fc * dt[e], zv[e]);
+        }
+        if (r0 == 0) base = uniform(g[0]);
+        if (on[0]) {
+            V* cells = strip + (g[0] - base);
+            T ta[W], tb[W];
+            node_taps<T, W, NE>(poly, u[0], ta);
+            node_taps<T, W, NE>(poly, u[1], tb);
+            if (pair) {
+                if (!on[1]) c[1] = cpx<T>{T(0), T(0)};
+                const bool same = !on[1] || g[1] == g[0];
+#pragma unroll
+                for (int t = 0; t <= W; ++t) {
+                    const T b = same ? (t < W ? tb[t < W ? t : 0] : T(0)) : (t > 0 ? tb[t > 0 ? t - 1 : 0] : T(0));
+                    V v = cells[t];
+                    if (t < W) {
+                        v.x = fma(ta[t < W ? t : 0], c[0].x, v.x);
+                        v.y = fma(ta[t < W ? t : 0], c[0].y, v.y);
+                    }
+                    v.x = fma(b, c[1].x, v.x);
+                    v.y = fma(b, c[1].y, v.y);
+                    cells[t] = v;
+                    lane_order();
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < W; ++t) {
+                    V v = cells[t];
+                    v.x = fma(ta[t], c[0].x, v.x);
+                    v.y = fma(ta[t], c[0].y, v.y);
+                    cells[t] = v;
+                    lane_order();
+                }
+            }
+        }
+        lane_order();
+        if (!pair && on[1]) {
+            V* cells = strip + (g[1] - base);
+            T tb[W];
+            node_taps<T, W, NE>(poly, u[1], tb);
+#pragma unroll
+            for (int t = 0; t < W; ++t) {
+                V v = cells[t];
+                v.x = fma(tb[t], c[1].x, v.x);
+                v.y = fma(tb[t], c[1].y, v.y);
+                cells[t] = v;
+                lane_order();
+            }
+        }
+        lane_order();
+    }
+    return base + 1;      // tap 0 of S lands on cell floor(S) + 1
+}
+
+// The outputs of bin k of an instance, as the fused epilogue writes them:
+// power rows (mode 1) or spectra and power at the bin offsets (mode 2).
+template <typename T>
+__device__ __forceinline__ void node_store(const NodeArgs& a, const EpilogueOut& o, const InstDev& d, int k, cpx<T> X)
+{
+    if (o.out_fp64) {
+        const double pw = (double)X.x * (double)X.x + (double)X.y * (double)X.y;
+        if (o.mode == 1) {
+            reinterpret_cast<double*>(o.rows)[a.row_base + (int64_t)d.entry * a.kmax + k] = pw;
+        } else {
+            if (o.spectra) reinterpret_cast<cpx<double>*>(o.spectra)[d.bin_off + k] = cpx<double>{(double)X.x, (double)X.y};
+            if (o.power) reinterpret_cast<double*>(o.power)[d.bin_off + k] = pw;
+        }
+    } else {
+        const float pw = (float)X.x * (float)X.x + (float)X.y * (float)X.y;
+        if (o.mode == 1) {
+            reinterpret_cast<float*>(o.rows)[a.row_base + (int64_t)d.entry * a.kmax + k] = pw;
+        } else {
+            if (o.spectra) reinterpret_cast<cpx<float>*>(o.spectra)[d.bin_off + k] = cpx<float>{(float)X.x, (float)X.y};
+            if (o.power) reinterpret_cast<float*>(o.power)[d.bin_off + k] = pw;
+        }
+    }
+}
+
+__device__ __forceinline__ int floor_mod(int x, int n)
+{
+    const int r = x % n;
+    return r < 0 ? r + n : r;
+}
+
+// Sum of the strip's cells that fold onto cell x of the periodic grid (base:
+// the strip's first cell modulo n).
+template <typename T, typename V>
+__device__ __forceinline__ cpx<T> node_fold(const V* strip, int base, int len, int x, int n)
+{
+    int p = x - base;
+    if (p < 0) p += n;
+    cpx<T> s{T(0), T(0)};
+    for (; p < len; p += n) {
+        const V v = strip[p];
+        s.x += v.x;
+        s.y += v.y;
+    }
+    return s;
+}
+
+// Small grids (n <= kNodeDftMax): a workgroup takes 16 instances, four per
+// wave, spreads each onto a strip of unwrapped cells in LDS, folds the strip
+// onto the periodic grid in place (real parts, then imaginary parts), and
+// transforms the 16 grids at once: X = F G with F [2 K][2 n] the DFT of the
+// wanted modes with the deconvolution in its rows, a 16-column matrix product.
+template <typename T, int W, int NE>
+__global__ __launch_bounds__(kBlock) void node_spread_dft_kernel(NodeArgs a, EpilogueOut o)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    T* lds = reinterpret_cast<T*>(smem_raw);
+    const int wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int n = a.n, gs = a.gstride, imo = a.im_off;
+    const int64_t item0 = (int64_t)blockIdx.x * kNodeBatch;
+    for (int q = threadIdx.x; q < kNodeBatch * gs; q += kBlock) lds[q] = T(0);
+    __syncthreads();
+#pragma unroll 1
+    for (int q = 0; q < kNodeBatch / 4; ++q) {
+        const int64_t item = item0 + wave * (kNodeBatch / 4) + q;
+        if (item >= a.count) break;
+        const InstDev d = load_inst(a.inst + item);
+        T* grid = lds + (wave * (kNodeBatch / 4) + q) * gs;
+        auto* strip = reinterpret_cast<typename Cell<T>::v*>(grid);
+        const int base = floor_mod(node_strip<T, W, NE>(d, a, 0, d.nodes, lane, strip), n);
+        cpx<T> v[kNodeDftMax / kWave];
+#pragma unroll
+        for (int e = 0; e < kNodeDftMax / kWave; ++e)
+            if (lane + e * kWave < n) v[e] = node_fold<T>(strip, base, a.strip, lane + e * kWave, n);
+        lane_order();
+#pragma unroll
+        for (int e = 0; e < kNodeDftMax / kWave; ++e)
+            if (lane + e * kWave < n) {
+                grid[lane + e * kWave] = v[e].x;
+                grid[imo + lane + e * kWave] = v[e].y;
+            }
+    }
+    __syncthreads();
+    const int nn = lane & 15, kq = lane >> 4;
+    const T* __restrict__ col = lds + nn * gs + kq;
+    const int half = a.ksteps / 2;
+    const int64_t item = item0 + nn;
+    for (int tile = wave; tile < a.mtiles; tile += 4) {
+        const T* __restrict__ A = reinterpret_cast<const T*>(a.dft) + (int64_t)tile * a.ksteps * 64 + lane;
+        typename Mfma<T>::acc c0{}, c1{};
+        for (int ks = 0; ks < half; ++ks) {
+            c0 = Mfma<T>::step(A[ks * 64], col[4 * ks], c0);
+            c1 = Mfma<T>::step(A[(half + ks) * 64], col[imo + 4 * ks], c1);
+        }
+        if (item >= a.count) continue;
+        const InstDev* __restrict__ d = a.inst + item;
+        const int K = d->K, q0 = 8 * tile + 2 * kq - a.m0max + d->m0;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int k = q0 + e;
+            if (k < 0 || k >= K) continue;
+            const T xr = c0[2 * e] + c1[2 * e], xi = c0[2 * e + 1] + c1[2 * e + 1];
+            node_store<T>(a, o, *d, k, cpx<T>{xr, xi});
+        }
+    }
+}
+
+// Large grids: a workgroup takes one instance; its four waves spread a
+// quarter of the nodes each onto a strip of their own, the strips are folded
+// onto the periodic grid and the workgroup runs the Stockham FFT (the grid at
+// the start of LDS, its other half over the strips).
+template <typename T, int W, int NE>
+__global__ __launch_bounds__(kBlock) void node_spread_fft_kernel(NodeArgs a, EpilogueOut o)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ int bases[4];
+    cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
+    const int wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int n = a.n, len = a.strip;
+    using V = typename Cell<T>::v;
+    V* strips = reinterpret_cast<V*>(lds + n);
+    const int64_t item = blockIdx.x;
+    for (int q = threadIdx.x; q < 4 * len; q += kBlock) strips[q] = V{T(0), T(0)};
+    __syncthreads();
+    const InstDev d = load_inst(a.inst + item);
+    const int per = (d.nodes + 3) / 4, first = wave * per;
+    const int count = d.nodes - first < per ? d.nodes - first : per;
+    int base = 0;
+    if (count > 0) base = node_strip<T, W, NE>(d, a, first, count, lane, strips + wave * len);
+    if (lane == 0) bases[wave] = floor_mod(base, n);
+    __syncthreads();
+    for (int c = threadIdx.x; c < n; c += kBlock) {
+        cpx<T> s{T(0), T(0)};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const cpx<T> v = node_fold<T>(strips + q * len, bases[q], len, c, n);
+            s.x += v.x;
+            s.y += v.y;
+        }
+        lds[c] = s;
+    }
+    __syncthreads();
+    const cpx<T>* res = fft_team<T>(lds, reinterpret_cast<const cpx<T>*>(a.twiddle), a.fft, threadIdx.x, kBlock);
+    const T* __restrict__ dec = reinterpret_cast<const T*>(a.dec);
+    for (int k = threadIdx.x; k < d.K; k += kBlock) {
+        int l = k - d.m0;
+        if (l < 0) l += n;
+        const T f = dec[l];
+        node_store<T>(a, o, d, k, cpx<T>{res[l].x * f, res[l].y * f});
+    }
+}
+
+// -------------------------------------------------------------- launches --
+
+size_t filter_lds_bytes(int fp64, int D, int Q, int ksteps, int images)
+{
+    const int kp = 16 * ksteps, reach = images / 2 * Q + kp;
+    return (size_t)((kNodeTile - 1) * D + 2 * reach + 1 + kp * ((images + 3) / 4 * 4)) * (fp64 ? 8 : 4);
+}
+
+template <typename T, typename Ti, int I>
+static hipError_t launch_node_filter_k(const FilterItem* items, int64_t count, size_t lds, const void* carriers,
+                                       const void* window, const void* strain, void* z, hipStream_t st)
+{
+    allow_lds(node_filter_kernel<T, Ti, I>, lds);
+    node_filter_kernel<T, Ti, I><<<dim3((unsigned)count), dim3(kBlock), lds, st>>>(
+        items, (const Ti*)strain, (const T*)carriers, (const T*)window, (cpx<T>*)z);
+    return hipGetLastError();
+}
+
+hipError_t launch_node_filter(const FilterItem* items, int64_t count, size_t lds, const void* carriers,
+                              const void* window, const void* strain, void* z, int strain_fp64, int fp64,
+                              hipStream_t st)
+{
+    if (count <= 0) return hipSuccess;
+    if (fp64) return launch_node_filter_k<double, double, kImages64>(items, count, lds, carriers, window, strain, z, st);
+    if (strain_fp64)
+        return launch_node_filter_k<float, double, kImages32>(items, count, lds, carriers, window, strain, z, st);
+    return launch_node_filter_k<float, float, kImages32>(items, count, lds, carriers, window, strain, z, st);
+}
+
+template <typename T, int W, int NE>
+static hipError_t launch_node_spread_k(const NodeArgs& a, const EpilogueOut& o, hipStream_t st)
+{
+    if (a.mtiles > 0) {
+        const size_t lds = (size_t)kNodeBatch * a.gstride * sizeof(T);
+        allow_lds(node_spread_dft_kernel<T, W, NE>, lds);
+        node_spread_dft_kernel<T, W, NE>
+            <<<dim3((unsigned)((a.count + kNodeBatch - 1) / kNodeBatch)), dim3(kBlock), lds, st>>>(a, o);
+    } else {
+        const size_t lds = node_fft_lds_bytes(sizeof(T) == 8, a.n, a.strip);
+        allow_lds(node_spread_fft_kernel<T, W, NE>, lds);
+        node_spread_fft_kernel<T, W, NE><<<dim3((unsigned)a.count), dim3(kBlock), lds, st>>>(a, o);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_node_spread(const NodeArgs& a, int fp64, const EpilogueOut& o, hipStream_t st)
+{
+    if (a.count <= 0) return hipSuccess;
+    if (!fp64 && a.w == 8) return launch_node_spread_k<float, 8, 4>(a, o, st);
+    if (fp64 && a.w == 12) return launch_node_spread_k<double, 12, 7>(a, o, st);
+    if (fp64 && a.w == 14) return launch_node_spread_k<double, 14, 9>(a, o, st);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace nr

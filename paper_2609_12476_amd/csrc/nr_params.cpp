@@ -19,8 +19,8 @@ const long double kPi = 3.14159265358979323846264338327950288L;
 const double kErrSigma2[17] = {1.0,    1.0,    9.0e-2, 1.1e-2, 9.9e-4, 1.8e-4,
                                1.6e-5, 1.5e-6, 1.4e-7, 1.7e-8, 3.2e-9, 3.1e-10,
                                3.3e-11, 2.3e-12, 4.0e-13, 3.0e-13, 3.0e-13};
+}  // namespace
 
-// Gauss-Legendre nodes/weights on [-1, 1] by Newton iteration on P_N.
 void gauss_legendre(int N, std::vector<long double>& x, std::vector<long double>& w)
 {
     x.resize(N);
@@ -44,7 +44,6 @@ void gauss_legendre(int N, std::vector<long double>& x, std::vector<long double>
         w[i] = 2.0L / ((1.0L - z * z) * dp * dp);
     }
 }
-}  // namespace
 
 double chirp_beta(double mc_msun, double f0)
 {
@@ -103,17 +102,17 @@ int kernel_pieces(int w, double beta, double tol, int max_deg, std::vector<long 
 {
     const int N = 96;  // Chebyshev interpolation nodes per piece
     const long double h = 0.5L * w;
-    std::vector<long double> coef((size_t)w * N);
+    std::vector<long double> coef((size_t)w * N), cosine(4 * N);
+    for (int q = 0; q < 4 * N; ++q) cosine[q] = cosl(kPi * q / (2 * N));   // period 4 N
     for (int t = 0; t < w; ++t) {
         std::vector<long double> f(N);
         for (int k = 0; k < N; ++k) {
-            const long double u = cosl(kPi * (k + 0.5L) / N);
-            const long double fr = 0.5L * (u + 1.0L);
+            const long double fr = 0.5L * (cosine[2 * k + 1] + 1.0L);
             f[k] = es_value(beta, (t + fr - h) / h);
         }
-        for (int p = 0; p < N; ++p) {
+        for (int p = 0; p <= max_deg; ++p) {
             long double s = 0.0L;
-            for (int k = 0; k < N; ++k) s += f[k] * cosl(p * kPi * (k + 0.5L) / N);
+            for (int k = 0; k < N; ++k) s += f[k] * cosine[p * (2 * k + 1) % (4 * N)];
             coef[(size_t)t * N + p] = (p == 0 ? 1.0L : 2.0L) * s / N;
         }
     }
@@ -153,6 +152,29 @@ int kernel_pieces(int w, double beta, double tol, int max_deg, std::vector<long 
     for (int t = 0; t < w; ++t)
         for (int p = 0; p <= best_deg; ++p) out[(size_t)t * (best_deg + 1) + p] = coef[(size_t)t * N + p];
     return best_deg;
+}
+
+std::vector<long double> node_filter_taps(int D, int half, double attenuation_db)
+{
+    // Kaiser's shape parameter and window I0(beta sqrt(1 - x^2)) / I0(beta)
+    const long double beta = 0.1102L * ((long double)attenuation_db - 8.7L);
+    auto i0 = [](long double x) {
+        const long double q = 0.25L * x * x;
+        long double term = 1.0L, sum = 1.0L;
+        for (int k = 1; term > 1e-22L * sum; ++k) {
+            term *= q / ((long double)k * k);
+            sum += term;
+        }
+        return sum;
+    };
+    const int n = half * D;
+    const long double scale = i0(beta);
+    std::vector<long double> h((size_t)n);
+    for (int k = 0; k < n; ++k) {
+        const long double x = (long double)k / n, t = kPi * k / D;
+        h[k] = (k == 0 ? 1.0L : k % D == 0 ? 0.0L : sinl(t) / t) * i0(beta * sqrtl(1.0L - x * x)) / scale;
+    }
+    return h;
 }
 
 int fft_size(long long m)

@@ -34,8 +34,16 @@ int kernel_pieces(int w, double beta, double tol, int max_deg, std::vector<long 
 //   psi_hat(xi) = int_{-w/2}^{w/2} exp(beta (sqrt(1 - (2x/w)^2) - 1)) cos(xi x) dx.
 long double es_fourier(int w, double beta, long double xi);
 
+// Gauss-Legendre nodes and weights on [-1, 1] (Newton iteration on P_N).
+void gauss_legendre(int N, std::vector<long double>& x, std::vector<long double>& w);
+
 // ES kernel value at z in [-1, 1].
 long double es_value(double beta, long double z);
+
+// Interpolation kernel of the node path at sample distances k = 0 .. half D - 1
+// of nodes D samples apart: sinc(k / D) under a Kaiser window of half-width
+// half D for the given attenuation in dB.
+std::vector<long double> node_filter_taps(int D, int half, double attenuation_db);
 
 // Smallest 2^a 3^b 5^c >= m.
 int fft_size(long long m);

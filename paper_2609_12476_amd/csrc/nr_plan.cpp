@@ -105,6 +105,13 @@ struct Chunk {
     int64_t order_off = -1;            // first entry of its workgroup order in Class::d_order (-1: none)
 };
 
+// Node choice of one instance (see plan_nodes).
+struct NodePick {
+    double centre;   // centre of its local frequencies, Hz
+    double lo, hi;   // least and largest dtau' over its nodes
+    int spacing;     // index into kNodeSpacing
+};
+
 struct Class {
     int fp64, w, n, deg, parts;
     int method = NR_METHOD_FUSED;
@@ -130,8 +137,13 @@ struct Class {
     int flush_period = 16;
     std::vector<int32_t> entry_seg;    // segment of each template-major list entry
     int64_t row_base = 0;              // two-pass sum: first element of the class's power rows
+    // node classes: spreading width (0: a sample class), per-instance centre
+    // of the local frequencies and index of the node spacing in kNodeSpacing
+    int node_w = 0;
+    int strip = 0;                     // cells of one wave's strip
+    std::vector<NodePick> picks;
     DevBuf d_inst, d_coef, d_taps, d_dec, d_tw, d_phase, d_strain, d_tmpl_id, d_tmpl_list,
-        d_tmpl_list_off, d_tmpl_stat_off, d_entry_seg, d_order;
+        d_tmpl_list_off, d_tmpl_stat_off, d_entry_seg, d_order, d_dft;
 };
 
 // XCD-aware workgroup order.  The GPU deals the workgroups of a launch to its
@@ -149,7 +161,7 @@ void build_block_order(Class& c)
     std::vector<int32_t> order;
     for (Chunk& ch : c.chunks) {
         ch.order_off = -1;
-        if (c.method == NR_METHOD_DIRECT) continue;
+        if (c.method == NR_METHOD_DIRECT || c.node_w) continue;
         const int64_t G = spread_blocks(ch.count, c.parts);
         if (G < kOrderMinBlocks || G > INT32_MAX) continue;
         std::vector<std::pair<int32_t, int32_t>> key((size_t)G);   // (segment of the first item, block)
@@ -224,6 +236,11 @@ struct nr_plan_s {
     std::vector<hipStream_t> side;
     hipEvent_t ev_fork[2] = {nullptr, nullptr};
     std::vector<hipEvent_t> ev_join[2];
+    // node classes: filter work, carriers, window and node values by precision
+    DevBuf d_filter[2], d_ftaps[2], d_fwin[2], d_z[2];
+    int64_t n_filter[2] = {0, 0};
+    size_t filter_lds[2] = {0, 0};
+    int64_t filter_macs[2] = {0, 0};
     int64_t n_invalid = 0;
     int64_t workspace = 0;
     int n_chunks = 0;
@@ -319,6 +336,7 @@ struct InstHost {
     double beta;
     long double a, c;  // tau scale and series variable per sample
     double y_max;
+    double us;         // u at the segment's start
 };
 
 // Validity rule and tau constants of one instance (long double host math);
@@ -330,6 +348,7 @@ InstHost instance_constants(const nr_segment& g, const nr_template& t, double be
     if (h.beta == 0.0) {
         h.valid = true;
         h.c = 1.0L / (long double)g.fs;
+        h.us = 1.0;
         return h;
     }
     const long double b = h.beta;
@@ -345,6 +364,7 @@ InstHost instance_constants(const nr_segment& g, const nr_template& t, double be
     h.a = (3.0L / (5.0L * b)) * powl(us, 5.0L / 8.0L);
     h.c = (8.0L / 3.0L) * b / (us * (long double)g.fs);
     h.y_max = (double)(h.c * (long double)(g.n_samples - 1));
+    h.us = (double)us;
     return h;
 }
 
@@ -483,13 +503,89 @@ int small_plan_parts(int64_t L)
 }
 
 struct ClassKey {
-    int fp64, w, n, parts, method, flush, snap, radix;
+    int fp64, w, n, parts, method, flush, snap, radix, node_w;
     bool operator<(const ClassKey& o) const
     {
-        return std::tie(fp64, w, n, parts, method, flush, snap, radix) <
-               std::tie(o.fp64, o.w, o.n, o.parts, o.method, o.flush, o.snap, o.radix);
+        return std::tie(fp64, w, n, parts, method, flush, snap, radix, node_w) <
+               std::tie(o.fp64, o.w, o.n, o.parts, o.method, o.flush, o.snap, o.radix, o.node_w);
     }
 };
+
+// ----------------------------------------------------------------- nodes --
+//
+// Instances of the automatic method whose templates share segments take the
+// node path (nr_nodes.hpp): the segment is filtered once per reference
+// frequency to band-limited values at nodes, and every instance resamples
+// those instead of its samples.
+
+// Samples between nodes, coarsest first (4 times an odd number: the filter's
+// LDS reads are then free of bank conflicts; but for 8 and 16, where twice
+// the nodes would cost more).
+constexpr int kNodeSpacing[] = {172, 148, 124, 100, 84, 76, 68, 60, 52, 44, 36, 28, 20, 16, 12, 8, 4};
+constexpr int kNodeSpacings = sizeof(kNodeSpacing) / sizeof(kNodeSpacing[0]);
+
+// Of the node rate R, the share between the edges of the pass band and of its
+// first image: the narrower, the fewer nodes and the longer the filter.
+constexpr double kNodeTransition = 0.35;
+// Reference frequencies are multiples of R / 6, so an instance's centre lies
+// within R / 12 of its own; with P the half-width of its local frequencies
+// P + R / 12 <= (1 - kNodeTransition) R / 2.  (The filter's products grow with
+// the square of kNodeRefs, the node rate falls slowly with it.)
+constexpr int kNodeRefs = 6;
+constexpr double kNodeMinRate = 1.0 / (0.5 * (1.0 - kNodeTransition) - 0.5 / kNodeRefs);
+
+// Spreading width of the node path for a class of width w, 0 where it has
+// none.  The path's own error lies far below the tolerance, so where it
+// changes an instance's result it is by the sample path's kernel error: FP32
+// classes of w >= 6 (error 1.6e-5 and less) and FP64 classes of w >= 11
+// (3.1e-10) take it, looser ones keep their values.
+int node_width(int fp64, int w)
+{
+    if (!fp64) return w >= 6 && w <= 8 ? 8 : 0;
+    return w >= 11 && w <= 12 ? 12 : w > 12 && w <= 14 ? 14 : 0;
+}
+
+// Attenuation of the filter in dB and its half-width in nodes (Kaiser's
+// estimate of the length of a window for that attenuation and transition).
+// FP32: 150 dB, 3e-8, half the rounding of one FP32 value.
+double node_attenuation(int fp64, int node_w) { return !fp64 ? 150.0 : node_w == 12 ? 230.0 : 270.0; }
+int node_half(int fp64, int node_w)
+{
+    const int half =
+        (int)std::ceil((node_attenuation(fp64, node_w) - 7.95) / (2.285 * 2.0 * M_PI * kNodeTransition) / 2.0);
+    return std::min(half, (fp64 ? kImages64 : kImages32) * kNodeRefs / 2);   // the window's images cover it
+}
+// Coefficients per parity of the node spreader's kernel pieces.
+int node_coefs(int node_w) { return node_w == 8 ? 4 : node_w == 12 ? 7 : 9; }
+int node_count(int64_t L, int D, int half) { return (int)((L - 1) / D) + 2 * half; }
+
+// Node choice of an instance: the coarsest spacing whose rate resolves its
+// local frequencies f dtau' over the span that its nodes cover (the segment
+// and the filter's half-width on either side); y_ext: the series variable at
+// the end of that span.  False if there is none.
+bool pick_nodes(const InstHost& h, const nr_segment& g, const nr_template& t, double df, int fp64, int node_w,
+                NodePick* pick, double* y_ext)
+{
+    const int half = node_half(fp64, node_w);
+    const double f0 = t.f_lo, f1 = t.f_lo + (t.n_bins - 1) * df;
+    const double c = h.beta == 0.0 ? 0.0 : (double)h.c;
+    const double r0 = h.beta == 0.0 ? 1.0 : std::pow(h.us, -0.375);
+    const double most = fp64 ? 84 : 172;          // the filter's window of samples stays in LDS
+    for (int s = 0; s < kNodeSpacings; ++s) {
+        const int D = kNodeSpacing[s];
+        // rates that do not even hold the band at rest need no closer look
+        if (D > most || g.fs < 0.5 * kNodeMinRate * (f1 - f0) * r0 * D) continue;
+        const double before = (double)(half - 1) * D, after = (double)(g.n_samples - 1) + (double)half * D;
+        if (c * after >= 0.9 || c * before >= 0.9) continue;
+        const double lo = r0 * std::pow(1.0 + c * before, -0.375), hi = r0 * std::pow(1.0 - c * after, -0.375);
+        const double a = std::min(f0 * lo, f0 * hi), b = std::max(f1 * lo, f1 * hi);
+        if (g.fs < kNodeMinRate * 0.5 * (b - a) * D) continue;
+        *pick = NodePick{0.5 * (a + b), lo, hi, s};
+        *y_ext = c * after;
+        return true;
+    }
+    return false;
+}
 
 // ------------------------------------------------------------- autotuner --
 
@@ -566,52 +662,384 @@ std::vector<T> cast_vec(const std::vector<long double>& v)
     return o;
 }
 
+// Upload long double values in the class's precision.
+void upload_as(DevBuf& b, int fp64, const std::vector<long double>& v, const char* what)
+{
+    if (fp64)
+        b.upload(cast_vec<double>(v), what);
+    else
+        b.upload(cast_vec<float>(v), what);
+}
+
+constexpr long double kPiL = 3.14159265358979323846264338327950288L;
+
+// exp(sign 2 pi i t / n), t < n, interleaved.
+std::vector<long double> roots_of_unity(int n, int sign)
+{
+    std::vector<long double> v(2 * (size_t)n);
+    for (int t = 0; t < n; ++t) {
+        const long double ang = sign * 2.0L * kPiL * t / n;
+        v[2 * t] = cosl(ang);
+        v[2 * t + 1] = sinl(ang);
+    }
+    return v;
+}
+
+// Deconvolution factors 1/psi_hat(2 pi l' / n), l' = min(l, n - l).
+std::vector<long double> deconvolution(int w, double beta_es, int n)
+{
+    std::vector<long double> dec(n);
+    for (int l = 0; l <= n / 2; ++l) {
+        dec[l] = 1.0L / es_fourier(w, beta_es, 2.0L * kPiL * l / n);
+        dec[(n - l) % n] = dec[l];
+    }
+    return dec;
+}
+
+// The same for the node spreader's kernel as its rounded polynomials have it
+// (poly: see build_class_tables), so that the rounding of the coefficients
+// does not scale the spectra (2.7e-8 of their amplitude in FP32).
+std::vector<long double> node_deconvolution(const std::vector<long double>& poly, int W, int NE, int fp64, int n)
+{
+    std::vector<long double> x, wq;
+    gauss_legendre(24, x, wq);
+    // kernel values times weights at the quadrature nodes of the first half of the pieces
+    std::vector<long double> at, val;
+    for (int t = 0; t < W / 2; ++t)
+        for (size_t q = 0; q < x.size(); ++q) {
+            long double v = 0.0L, up = 1.0L;
+            for (int k = 0; k < 2 * NE; ++k, up *= x[q]) {
+                const long double a = poly[(size_t)(t * 2 + (k & 1)) * NE + k / 2];
+                v += (fp64 ? (long double)(double)a : (long double)(float)a) * up;
+            }
+            at.push_back(t + 0.5L * (x[q] + 1.0L) - 0.5L * W);
+            val.push_back(wq[q] * v);                  // both halves: 2 x 1/2
+        }
+    std::vector<long double> dec(n);
+    for (int l = 0; l <= n / 2; ++l) {
+        long double s = 0.0L;
+        for (size_t q = 0; q < at.size(); ++q) s += val[q] * cosl(2.0L * kPiL * l / n * at[q]);
+        dec[l] = 1.0L / s;
+        dec[(n - l) % n] = dec[l];
+    }
+    return dec;
+}
+
 void build_class_tables(Class& c, double tol_cls, double sigma)
 {
     // Chebyshev pieces of the kernel and the degree that reaches the target
     std::vector<long double> taps;
     c.deg = kernel_pieces(c.w, c.beta_es, tol_cls, kMaxDeg, taps);
-    // deconvolution factors 1/psi_hat(2 pi l' / n), l' = min(l, n - l)
-    std::vector<long double> dec(c.n);
-    for (int l = 0; l < c.n; ++l) {
-        const int lp = std::min(l, c.n - l);
-        dec[l] = 1.0L / es_fourier(c.w, c.beta_es, 2.0L * 3.14159265358979323846264338327950288L * lp / c.n);
-    }
-    std::vector<long double> tw(2 * (size_t)c.n);
-    for (int t = 0; t < c.n; ++t) {
-        const long double ang = -2.0L * 3.14159265358979323846264338327950288L * t / c.n;
-        tw[2 * t] = cosl(ang);
-        tw[2 * t + 1] = sinl(ang);
-    }
     c.radix = c.radix_code ? radix_from_code(c.radix_code) : fft_radices(c.n);
+    const std::vector<long double> tw = roots_of_unity(c.n, -1);
+    if (c.node_w) {
+        // kernel pieces of the node spreader as powers of u, split by parity;
+        // the kernel is even, so the second half of the taps mirrors the first
+        const int W = c.node_w, NE = node_coefs(W);
+        const double beta = es_beta(W, sigma);
+        const int deg = kernel_pieces(W, beta, 0.0, 2 * NE - 1, taps);
+        std::vector<long double> poly((size_t)W * NE, 0.0L), t0, t1, t2;
+        for (int t = 0; t < W / 2; ++t) {
+            t0.assign(2 * NE, 0.0L);
+            t1.assign(2 * NE, 0.0L);
+            t0[0] = t1[1] = 1.0L;
+            for (int p = 0; p <= deg; ++p) {
+                const long double a = taps[(size_t)t * (deg + 1) + p];
+                for (int k = 0; k < 2 * NE; ++k) poly[(size_t)(t * 2 + (k & 1)) * NE + k / 2] += a * t0[k];
+                t2.assign(2 * NE, 0.0L);               // T_{p+2} = 2 u T_{p+1} - T_p
+                for (int k = 0; k < 2 * NE; ++k) t2[k] = (k ? 2.0L * t1[k - 1] : 0.0L) - t0[k];
+                t0.swap(t1);
+                t1.swap(t2);
+            }
+        }
+        upload_as(c.d_taps, c.fp64, poly, "kernel pieces");
+        const std::vector<long double> dec = node_deconvolution(poly, W, NE, c.fp64, c.n);
+        if (c.n > kNodeDftMax) {
+            upload_as(c.d_dec, c.fp64, dec, "deconvolution");
+            upload_as(c.d_tw, c.fp64, tw, "twiddles");
+            return;
+        }
+        // rows of the small DFT (see node_spread_dft_kernel): lane l of a step
+        // holds A[row l % 16][column l / 16], the columns being the grid's
+        // real, then its imaginary parts
+        const int half = (c.n + 3) / 4, tiles = (2 * c.kmax + 15) / 16, m0 = c.kmax / 2;
+        std::vector<long double> dft((size_t)tiles * 2 * half * 64, 0.0L);
+        for (int tile = 0; tile < tiles; ++tile)
+            for (int g = 0; g < 4; ++g)
+                for (int i = 0; i < 4; ++i) {
+                    const int row = mfma_row(c.fp64, g, i), q = 8 * tile + 2 * g + (i >> 1);
+                    if (q >= c.kmax) continue;
+                    const int m = ((q - m0) % c.n + c.n) % c.n;
+                    for (int cell = 0; cell < c.n; ++cell) {
+                        const int at = (int)((int64_t)m * cell % c.n);
+                        const long double re = dec[m] * tw[2 * at], im = dec[m] * tw[2 * at + 1];
+                        long double* d = dft.data() + (((size_t)tile * 2 * half + cell / 4) * 64 + (cell & 3) * 16 + row);
+                        d[0] = (i & 1) ? im : re;                       // times the real part
+                        d[(size_t)half * 64] = (i & 1) ? re : -im;      // times the imaginary part
+                    }
+                }
+        upload_as(c.d_dft, c.fp64, dft, "DFT rows");
+        return;
+    }
+    upload_as(c.d_taps, c.fp64, taps, "kernel pieces");
+    upload_as(c.d_dec, c.fp64, deconvolution(c.w, c.beta_es, c.n), "deconvolution");
+    upload_as(c.d_tw, c.fp64, tw, "twiddles");
     // coarse heterodyne phasors exp(2 pi i k / N)
-    const int NT = phase_table_size(c.fp64);
-    std::vector<long double> ph(2 * (size_t)NT);
-    for (int k = 0; k < NT; ++k) {
-        const long double ang = 2.0L * 3.14159265358979323846264338327950288L * k / NT;
-        ph[2 * k] = cosl(ang);
-        ph[2 * k + 1] = sinl(ang);
-    }
-    if (c.fp64) {
-        c.d_taps.upload(cast_vec<double>(taps), "kernel pieces");
-        c.d_dec.upload(cast_vec<double>(dec), "deconvolution");
-        c.d_tw.upload(cast_vec<double>(tw), "twiddles");
-        c.d_phase.upload(cast_vec<double>(ph), "phase table");
-    } else {
-        c.d_taps.upload(cast_vec<float>(taps), "kernel pieces");
-        c.d_dec.upload(cast_vec<float>(dec), "deconvolution");
-        c.d_tw.upload(cast_vec<float>(tw), "twiddles");
-        c.d_phase.upload(cast_vec<float>(ph), "phase table");
-    }
-    (void)sigma;
+    upload_as(c.d_phase, c.fp64, roots_of_unity(phase_table_size(c.fp64), 1), "phase table");
 }
 
 Tuned tuned_config(const nr_options& base, const nr_segment& g, const nr_template& t, double tol, int fp64,
                    int w, int n, int64_t small_batch);
 void build_groups(nr_plan_s& P);
 
-void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_template* tmpls,
-                 int32_t n_tmpls, const nr_instance* inst, int64_t n_inst, double tol)
+// LDS values of one instance of a small-grid node class: its strip, then in
+// place the grid's real and imaginary parts; 4 (mod 8), so that the 16 columns
+// of a matrix step fall on distinct banks.
+int node_stride(const Class& c)
+{
+    return (std::max(2 * c.strip, 8 * ((c.n + 3) / 4)) + 3) / 8 * 8 + 4;
+}
+size_t node_lds_bytes(const Class& c)
+{
+    return c.n <= kNodeDftMax ? (size_t)kNodeBatch * node_stride(c) * (c.fp64 ? 8 : 4)
+                              : node_fft_lds_bytes(c.fp64, c.n, c.strip);
+}
+
+// Place the node classes' instances on filtered node values, or return false
+// if the sample path would be cheaper.  Spacings of one shape are merged where
+// that saves more filters than it adds nodes; reference frequencies are grouped in tiles of 16, the rows of one matrix
+// product, and every (segment, tile) that an instance uses is filtered.
+bool plan_nodes(nr_plan_s& P)
+{
+    struct Shape {
+        int fp64, node_w;
+        double fs;
+        int64_t L;
+        bool operator<(const Shape& o) const
+        {
+            return std::tie(fp64, node_w, fs, L) < std::tie(o.fp64, o.node_w, o.fs, o.L);
+        }
+    };
+    struct Use {                       // one spacing of one shape
+        int64_t count = 0;
+        double f_lo = INFINITY, f_hi = -INFINITY;   // centres
+        int final_s = -1;              // the spacing it is merged into
+        int lo = INT32_MAX, hi = INT32_MIN;
+        std::vector<int> rank;         // of reference index - lo, -1 unused
+        int tiles = 0;
+        std::vector<int64_t> z_off;    // [segment][tile], -1 unused
+        std::vector<int> refs;         // by rank
+    };
+    std::map<Shape, std::array<Use, kNodeSpacings>> shapes;
+    auto each = [&](auto&& f) {
+        std::map<Shape, std::array<Use, kNodeSpacings>>::iterator it = shapes.end();
+        for (auto& cp : P.classes) {
+            Class& c = *cp;
+            for (size_t k = 0; k < c.picks.size(); ++k) {
+                const nr_segment& g = P.segs[c.inst[k].seg];
+                const Shape key{c.fp64, c.node_w, g.fs, g.n_samples};
+                if (it == shapes.end() || it->first < key || key < it->first) it = shapes.try_emplace(key).first;
+                f(c, c.inst[k], c.picks[k], it->first, it->second);
+            }
+        }
+    };
+    each([](Class&, InstDev&, NodePick& p, const Shape&, std::array<Use, kNodeSpacings>& u) {
+        Use& v = u[p.spacing];
+        ++v.count;
+        v.f_lo = std::min(v.f_lo, p.centre);
+        v.f_hi = std::max(v.f_hi, p.centre);
+    });
+    if (shapes.empty()) return false;
+    // lane-operations of one node round of an instance, and of the filter of
+    // one segment for `tiles` tiles
+    auto nodes_of = [](const Shape& sh, int s) {
+        return node_count(sh.L, kNodeSpacing[s], node_half(sh.fp64, sh.node_w));
+    };
+    auto spread_cost = [&](const Shape& sh, int s) {
+        return (double)((nodes_of(sh, s) + kWave - 1) / kWave) * kWave * (sh.fp64 ? 170.0 : 85.0);
+    };
+    // per 64 nodes: two products of 16 tiles x 64 x Q / 2 at twice the VALU's
+    // rate in FP32, and the folding
+    auto filter_cost = [&](const Shape& sh, int s, int tiles) {
+        const double chunks = (double)((nodes_of(sh, s) + kNodeTile - 1) / kNodeTile);
+        return chunks * kNodeTile * (0.5 * kNodeRefs * kNodeSpacing[s] + 8.0) *
+               (2.0 * tiles * kFilterRows * (sh.fp64 ? 1.0 : 0.5) + 5.0 * (sh.fp64 ? kImages64 : kImages32));
+    };
+    for (auto& kv : shapes) {
+        const Shape& sh = kv.first;
+        // from coarse to fine: a spacing joins the next finer one in use where
+        // its instances' additional nodes cost less than filters of its own
+        for (int s = 0; s < kNodeSpacings; ++s) {
+            Use& u = kv.second[s];
+            if (u.count == 0) continue;
+            u.final_s = s;
+            int next = s + 1;
+            while (next < kNodeSpacings && kv.second[next].count == 0) ++next;
+            if (next == kNodeSpacings) continue;
+            const double refs = (u.f_hi - u.f_lo) * kNodeRefs * kNodeSpacing[s] / sh.fs + 1.0;
+            const double own = filter_cost(sh, s, (int)std::min(1e6, std::ceil(refs / kFilterRows))) *
+                               (double)std::min<int64_t>(u.count, P.n_segs);
+            if ((double)u.count * (spread_cost(sh, next) - spread_cost(sh, s)) < own) {
+                Use& v = kv.second[next];
+                v.count += u.count;
+                v.f_lo = std::min(v.f_lo, u.f_lo);
+                v.f_hi = std::max(v.f_hi, u.f_hi);
+                u.final_s = next;
+            }
+        }
+        for (int s = kNodeSpacings - 1; s >= 0; --s) {
+            Use& u = kv.second[s];
+            if (u.final_s >= 0 && u.final_s != s) u.final_s = kv.second[u.final_s].final_s;
+        }
+    }
+    auto ref_of = [](const NodePick& p, const Shape& sh) {
+        return (int)std::lround(p.centre * (kNodeRefs * kNodeSpacing[p.spacing]) / sh.fs);
+    };
+    each([&](Class&, InstDev&, NodePick& p, const Shape& sh, std::array<Use, kNodeSpacings>& u) {
+        p.spacing = u[p.spacing].final_s;
+        Use& v = u[p.spacing];
+        const int r = ref_of(p, sh);
+        v.lo = std::min(v.lo, r);
+        v.hi = std::max(v.hi, r);
+    });
+    double samples_cost = 0.0, node_cost = 0.0;      // VALU lane-operations
+    for (auto& kv : shapes)
+        for (Use& u : kv.second)
+            if (u.lo <= u.hi) {
+                if ((int64_t)u.hi - u.lo > (int64_t(1) << 24)) return false;
+                u.rank.assign((size_t)(u.hi - u.lo + 1), -1);
+            }
+    each([&](Class& c, InstDev& d, NodePick& p, const Shape& sh, std::array<Use, kNodeSpacings>& u) {
+        u[p.spacing].rank[ref_of(p, sh) - u[p.spacing].lo] = 0;
+        // about 55 (73 in FP64) lane-operations a sample, 85 (170) a node
+        samples_cost += (double)d.L * (c.fp64 ? 73.0 : 55.0);
+        node_cost += spread_cost(sh, p.spacing);
+    });
+    for (auto& kv : shapes)
+        for (int s = 0; s < kNodeSpacings; ++s) {
+            Use& u = kv.second[s];
+            if (u.lo > u.hi) continue;
+            for (size_t r = 0; r < u.rank.size(); ++r)
+                if (u.rank[r] == 0) {
+                    u.rank[r] = (int)u.refs.size();
+                    u.refs.push_back(u.lo + (int)r);
+                }
+            u.tiles = ((int)u.refs.size() + kFilterRows - 1) / kFilterRows;
+            if ((int64_t)u.tiles * P.n_segs > (int64_t(1) << 26)) return false;
+            u.z_off.assign((size_t)u.tiles * P.n_segs, -1);
+        }
+    each([&](Class&, InstDev& d, NodePick& p, const Shape& sh, std::array<Use, kNodeSpacings>& u) {
+        Use& v = u[p.spacing];
+        v.z_off[(size_t)d.seg * v.tiles + v.rank[ref_of(p, sh) - v.lo] / kFilterRows] = 0;
+    });
+    std::vector<FilterItem> items[2];
+    std::vector<long double> carriers[2], window[2];
+    int64_t z[2] = {0, 0};
+    for (auto& kv : shapes)
+        for (int s = 0; s < kNodeSpacings; ++s) {
+            const Shape& sh = kv.first;
+            Use& u = kv.second[s];
+            if (u.lo > u.hi) continue;
+            const int f = sh.fp64, D = kNodeSpacing[s], half = node_half(f, sh.node_w), NB = node_count(sh.L, D, half);
+            const int Q = kNodeRefs * D, images = f ? kImages64 : kImages32, stride = (images + 3) / 4 * 4;
+            const int ksteps = (Q / 2 + 1 + 15) / 16;
+            FilterItem it{};
+            it.D = D;
+            it.Q = Q;
+            it.ksteps = ksteps;
+            it.L = (int32_t)sh.L;
+            it.nodes = NB;
+            it.j0 = -(half - 1) * D;
+            // the window's images k + Q i of folded sample k (k = 0 and Q / 2 are
+            // met from both sides: halved)
+            it.win_off = (int64_t)window[f].size();
+            const std::vector<long double> h = node_filter_taps(D, half, node_attenuation(f, sh.node_w));
+            window[f].resize(window[f].size() + (size_t)ksteps * 16 * stride, 0.0L);
+            for (int k = 0; k <= Q / 2; ++k)
+                for (int i = 0; i < images; ++i) {
+                    const int d = std::abs(k + Q * (i - images / 2));
+                    if (d < half * D)
+                        window[f][(size_t)it.win_off + (size_t)k * stride + i] = (k == 0 || 2 * k == Q ? 0.5L : 1.0L) * h[d];
+                }
+            const int64_t tap0 = (int64_t)carriers[f].size() / 2;
+            const std::vector<long double> root = roots_of_unity(Q, -1);
+            carriers[f].resize(carriers[f].size() + (size_t)u.tiles * ksteps * 512, 0.0L);
+            for (size_t r = 0; r < u.refs.size(); ++r) {
+                const int ref = (u.refs[r] % Q + Q) % Q;
+                long double* row = carriers[f].data() + 2 * tap0 + (r / kFilterRows) * (size_t)ksteps * 512 +
+                                   2 * (r % kFilterRows);
+                for (int k = 0; k <= Q / 2; ++k) {
+                    const int at = (int)((int64_t)ref * k % Q);
+                    long double* q = row + (size_t)(k / 4) * 128 + (k & 3) * 32;
+                    q[0] = root[2 * at];
+                    q[1] = root[2 * at + 1];
+                }
+            }
+            P.filter_lds[f] = std::max(P.filter_lds[f], filter_lds_bytes(f, D, Q, ksteps, images));
+            for (int32_t g = 0; g < P.n_segs; ++g)
+                for (int t = 0; t < u.tiles;) {
+                    int64_t* at = &u.z_off[(size_t)g * u.tiles + t];
+                    int run = 0;
+                    while (run < kFilterTiles && t + run < u.tiles && at[run] >= 0) {
+                        at[run] = z[f] + (int64_t)run * kFilterRows * NB;
+                        ++run;
+                    }
+                    if (run > 0) {
+                        it.src_off = P.segs[g].sample_offset;
+                        it.z_off = z[f];
+                        it.tap_off = tap0 + (int64_t)t * ksteps * 256;
+                        it.tiles = run;
+                        for (it.node0 = 0; it.node0 < NB; it.node0 += kNodeTile) items[f].push_back(it);
+                        z[f] += (int64_t)run * kFilterRows * NB;
+                        node_cost += filter_cost(sh, s, run);
+                        P.filter_macs[f] += (int64_t)((NB + kNodeTile - 1) / kNodeTile) * kNodeTile * 16 * ksteps *
+                                            (2 * run * kFilterRows + 2 * images);
+                    }
+                    t += std::max(run, 1);
+                }
+        }
+    if (node_cost > 0.5 * samples_cost) return false;
+    double worst = 0.0;
+    each([&](Class& c, InstDev& d, NodePick& p, const Shape& sh, std::array<Use, kNodeSpacings>& u) {
+        const Use& v = u[p.spacing];
+        const int half = node_half(sh.fp64, sh.node_w), rank = v.rank[ref_of(p, sh) - v.lo];
+        d.C = kNodeSpacing[p.spacing];
+        d.nodes = node_count(sh.L, d.C, half);
+        // cells from one node to the next, at least and at most; a lane's nodes
+        // (consecutive ones) put a cell between it and the next lane
+        const double cells = c.n * d.df * d.C / sh.fs;
+        const int apart = (int)std::min(1e6, std::ceil(1.0 / (cells * p.lo) + 1e-6));
+        const int per = c.n <= kNodeDftMax ? d.nodes : (d.nodes + 3) / 4;
+        worst = std::max({worst, (double)apart / 64.0, cells * p.hi * per / 65536.0});
+        c.strip = std::max(c.strip, (int)std::min(1e6, std::ceil(cells * p.hi * per)) + c.node_w + 3);
+        const int pair = cells * p.hi < 1.0 ? 1 << 16 : 0;
+        d.pt_off = (int64_t)(((uint64_t)(pair | (apart - 1)) << 32) | (uint32_t)(-(half - 1) * d.C));
+        d.strain_off = v.z_off[(size_t)d.seg * v.tiles + rank / kFilterRows] + (int64_t)(rank % kFilterRows) * d.nodes;
+    });
+    // nodes far closer than cells, or bins so far apart that the series winds
+    // round the grid many times: the sample path
+    if (worst > 1.0) return false;
+    for (auto& cp : P.classes)
+        if (cp->node_w && node_lds_bytes(*cp) > (cp->n <= kNodeDftMax ? kLdsBytes / 2 : kLdsBytes)) return false;
+    const int64_t cap = P.opt.max_workspace_bytes > 0 ? P.opt.max_workspace_bytes : (int64_t(8) << 30);
+    if (z[0] * 8 + z[1] * 16 > cap) return false;
+    for (int f = 0; f < 2; ++f) {
+        if (items[f].empty()) continue;
+        if (items[f].size() > (size_t)INT32_MAX) return false;
+        P.n_filter[f] = (int64_t)items[f].size();
+        P.d_filter[f].upload(items[f], "filter work");
+        upload_as(P.d_ftaps[f], f, carriers[f], "filter carriers");
+        upload_as(P.d_fwin[f], f, window[f], "filter window");
+        P.d_z[f].alloc((size_t)z[f] * (f ? 16 : 8), "node values");
+    }
+    return true;
+}
+
+// Build the plan; nodes: instances that can take the node path do.  False
+// (with nodes only) if the sample path serves the plan better or the node
+// path does not fit the workspace: the plan is then half built.
+bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs, const nr_template* tmpls,
+                int32_t n_tmpls, const nr_instance* inst, int64_t n_inst, double tol)
 {
     const nr_options& o = P.opt;
     validate(segs, n_segs, tmpls, n_tmpls, inst, n_inst, tol, o);
@@ -702,7 +1130,7 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
     }
     // kernel width per distinct tolerance, and the last class looked up
     std::map<std::pair<double, int>, int> width_of;
-    ClassKey last_key{-1, -1, -1, -1, -1, -1, -1, -1};
+    ClassKey last_key{-1, -1, -1, -1, -1, -1, -1, -1, -1};
     std::vector<double> series;
     size_t last_ci = 0;
     for (int64_t i = 0; i < N; ++i) {
@@ -737,10 +1165,23 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
         const double df_i = t.df > 0.0 ? t.df : g.fs / (double)g.n_samples;
         series.clear();
         int ndeg = 0;
+        int node_w = nodes ? node_width(fp64, w) : 0;
+        NodePick pick{};
+        double y_ext = 0.0;
+        if (node_w && !pick_nodes(h, g, t, df_i, fp64, node_w, &pick, &y_ext)) node_w = 0;
         double phase_steps = 0.0;   // heterodyne phase span in phase-table steps
         if (h.beta != 0.0) {
             const double f_ref = std::fabs(t.f_lo) + (double)K * df_i + df_i;
-            ndeg = horner_series(h, f_ref, fp64 ? 1e-14 : 1e-11, series);
+            if (node_w) {
+                InstHost he = h;
+                he.y_max = y_ext;
+                ndeg = horner_series(he, f_ref, fp64 ? 1e-14 : 1e-11, series);
+                if (ndeg < 0) {
+                    node_w = 0;
+                    series.clear();
+                }
+            }
+            if (!node_w) ndeg = horner_series(h, f_ref, fp64 ? 1e-14 : 1e-11, series);
         }
         {
             // The heterodyne phase fc dtau is evaluated in FP64: the tau
@@ -770,14 +1211,17 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
                          " rad, too coarse for tolerance " + std::to_string(tol_eff));
         }
         int method = resolve_method(o.method);
-        if (o.method == NR_METHOD_AUTO &&
+        if (node_w) method = NR_METHOD_CELLRUN;
+        if (o.method == NR_METHOD_AUTO && !node_w &&
             ((double)g.n_samples >= (small_plan && plan_waves < kLargePlanWaves ? kCellRunMinDensity
                                                                                 : kCellRunMinDensityLarge) *
                                         cells_visited(h, g.n_samples, n, df_i) ||
              spread_lds_bytes(fp64, n) <= kCellRunMaxSparseLds))
             method = NR_METHOD_CELLRUN;
         int parts = o.parts ? o.parts : small_plan ? small_plan_parts(g.n_samples) : default_parts(g.n_samples);
-        if (method == NR_METHOD_CELLRUN && o.parts == 0)
+        if (node_w)
+            parts = 1;
+        else if (method == NR_METHOD_CELLRUN && o.parts == 0)
             parts = cellrun_parts(cellrun_rounds(h, g.n_samples, n, df_i), small_plan, g.n_samples, plan_waves);
         int flush = o.flush_period;
         int snap = o.moment_mode == 2 ? 1 : 0;
@@ -805,9 +1249,9 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
         // conversion of the phase in table steps; longer phase spans take the
         // staged path, whose tau kernel reduces the phase modulo one cycle
         // (FP32 classes: phase_steps is 0, they have no table)
-        if (phase_steps >= kFusedMaxPhaseSteps && method != NR_METHOD_DIRECT) method = NR_METHOD_STAGED;
+        if (phase_steps >= kFusedMaxPhaseSteps && method != NR_METHOD_DIRECT && !node_w) method = NR_METHOD_STAGED;
         if (method == NR_METHOD_CELLRUN) snap = 0;  // moments restart with every run
-        ClassKey key{fp64, w, n, parts, method, flush, snap, radix};
+        ClassKey key{fp64, w, n, parts, method, flush, snap, radix, node_w};
         size_t ci;
         const bool same = !(key < last_key) && !(last_key < key);
         auto it = same ? class_of.end() : class_of.find(key);
@@ -827,6 +1271,7 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
             c->flush_period = flush;
             c->snap = snap;
             c->radix_code = radix;
+            c->node_w = node_w;
             c->beta_es = es_beta(w, sigma);
             P.classes.push_back(std::move(c));
         } else {
@@ -857,17 +1302,19 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
             d.coef_off = (int32_t)c.coef.size();
             c.coef.insert(c.coef.end(), series.begin(), series.end());
         }
+        if (node_w) c.picks.push_back(pick);
         c.inst.push_back(d);
         c.kmax = std::max(c.kmax, K);
         c.n_points += g.n_samples;
     }
+    if (nodes && !plan_nodes(P)) return false;
     for (auto& kv : class_of) build_class_tables(*P.classes[kv.second], class_tol[kv.first], sigma);
 
     // Lane-major strain layout per class, point-stream offsets, templates
     const size_t psize_f = 8, psize_d = 16;
     int64_t grid_chunk_bytes = 0, point_chunk_bytes = 0, grid_total = 0, point_total = 0;
     const int64_t cap = o.max_workspace_bytes > 0 ? o.max_workspace_bytes : (int64_t(8) << 30);
-    int64_t fixed_bytes = 0;
+    int64_t fixed_bytes = (int64_t)(P.d_z[0].bytes + P.d_z[1].bytes);
     for (auto& cp : P.classes) {
         Class& c = *cp;
         std::vector<int64_t> seg_at(P.n_segs, -1);
@@ -877,7 +1324,7 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
         std::vector<std::vector<int32_t>> lists;
         for (size_t k = 0; k < c.inst.size(); ++k) {
             InstDev& d = c.inst[k];
-            if (seg_at[d.seg] < 0) {
+            if (!c.node_w && seg_at[d.seg] < 0) {
                 SegDev sd{};
                 sd.src_off = P.segs[d.seg].sample_offset;
                 sd.dst_off = c.strain_entries;
@@ -890,9 +1337,11 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
                 seg_at[d.seg] = sd.dst_off;
                 c.strain_entries += (int64_t)sd.parts * d.C * kWave;
             }
-            d.strain_off = seg_at[d.seg];
-            d.pt_off = pt;
-            pt += (int64_t)c.parts * d.C * kWave;
+            if (!c.node_w) {
+                d.strain_off = seg_at[d.seg];
+                d.pt_off = pt;
+                pt += (int64_t)c.parts * d.C * kWave;
+            }
             d.bin_off = P.bin_off[d.inst];
             const int32_t pm = P.inst_tmpl[d.inst];
             if (tmpl_at[pm] < 0) {
@@ -931,9 +1380,9 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
             for (int32_t k : lists[t]) ct_of[k] = (int32_t)t;
         fixed_bytes += c.strain_entries * esize;
         // chunks bounded by the workspace cap
-        // the direct baseline needs no grid
+        // the direct baseline and the node classes need no grid
         const int64_t gsize =
-            c.method == NR_METHOD_DIRECT ? 0 : (int64_t)c.n * (c.fp64 ? 16 : 8) * grid_slots(c.parts);
+            c.method == NR_METHOD_DIRECT || c.node_w ? 0 : (int64_t)c.n * (c.fp64 ? 16 : 8) * grid_slots(c.parts);
         const int64_t psz = c.method == NR_METHOD_STAGED ? (c.fp64 ? psize_d : psize_f) : 0;
         const int64_t budget = std::max<int64_t>(cap / 2, 1);
         int64_t k0 = 0;
@@ -972,7 +1421,7 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
             const bool fits = c.method != NR_METHOD_DIRECT && c.parts <= 4 &&
                               lds_tier(spread_lds_bytes(c.fp64, c.n, c.parts == 1)) >=
                                   lds_tier(spread_lds_bytes(c.fp64, c.n, 0));
-            c.fuse_epi = wanted && fits ? 1 : 0;
+            c.fuse_epi = (wanted && fits) || c.node_w ? 1 : 0;
         }
         build_block_order(c);
         // device tables
@@ -993,8 +1442,9 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
         P.workspace += (int64_t)(c.d_inst.bytes + c.d_coef.bytes + c.d_strain.bytes +
                                  c.d_phase.bytes + c.d_taps.bytes + c.d_dec.bytes + c.d_tw.bytes + c.d_tmpl_id.bytes +
                                  c.d_tmpl_list.bytes + c.d_tmpl_list_off.bytes + c.d_tmpl_stat_off.bytes +
-                                 c.d_entry_seg.bytes + c.d_order.bytes);
+                                 c.d_entry_seg.bytes + c.d_order.bytes + c.d_dft.bytes);
     }
+    if (nodes && fixed_bytes + grid_chunk_bytes + point_chunk_bytes > cap) return false;
     if (fixed_bytes + grid_chunk_bytes + point_chunk_bytes > cap)
         fail(NR_ERR_OUT_OF_MEMORY, "workspace of " + std::to_string(fixed_bytes + grid_chunk_bytes + point_chunk_bytes) +
                                        " bytes exceeds max_workspace_bytes " + std::to_string(cap));
@@ -1012,7 +1462,7 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
             Class& c = *cp;
             c.grid_off = go;
             c.pts_off = po;
-            const int64_t gsize = (int64_t)c.n * (c.fp64 ? 16 : 8) * grid_slots(c.parts);
+            const int64_t gsize = c.node_w ? 0 : (int64_t)c.n * (c.fp64 ? 16 : 8) * grid_slots(c.parts);
             go += (int64_t)c.inst.size() * gsize;
             if (c.method == NR_METHOD_STAGED)
                 po += c.pt_entries * (c.fp64 ? (int64_t)psize_d : (int64_t)psize_f);
@@ -1033,6 +1483,8 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
         const int64_t rbytes = rows * (P.out_fp64 ? 8 : 4);
         P.two_pass = one_chunk && !P.classes.empty() &&
                      fixed_bytes + grid_chunk_bytes + point_chunk_bytes + rbytes <= cap;
+        // node classes write power rows: without them the sample path takes over
+        if (nodes && !P.two_pass) return false;
         if (P.two_pass) P.d_rows.alloc((size_t)rbytes, "power rows");
         if (any_direct && !P.two_pass)
             fail(NR_ERR_OUT_OF_MEMORY, "the direct method needs every class in one chunk with its power rows "
@@ -1074,6 +1526,34 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
     P.workspace += (int64_t)(P.d_grid.bytes + P.d_points.bytes + P.d_mask.bytes + P.d_invalid.bytes + P.d_rows.bytes +
                              P.d_lm_segs[0].bytes + P.d_lm_segs[1].bytes +
                              P.d_bin_off.bytes + P.d_inst_K.bytes + P.d_flag.bytes);
+    for (int f = 0; f < 2; ++f) P.workspace += (int64_t)(P.d_filter[f].bytes + P.d_ftaps[f].bytes + P.d_fwin[f].bytes + P.d_z[f].bytes);
+    return true;
+}
+
+// Options that leave the spreader to the plan and real strain: the node path
+// may serve the plan.  The static-scratch entry point plans on every call and
+// keeps the sample path, whose plan is shorter.
+bool nodes_allowed(const nr_options& o, int radix_override)
+{
+    return o.method == NR_METHOD_AUTO && !o.strain_complex && !o.tune && o.parts == 0 && o.flush_period == 0 &&
+           o.moment_mode == 0 && o.epilogue == 0 && (o.sigma <= 0.0 || o.sigma == 2.0) && radix_override == 0 && !g_arena;
+}
+
+void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_template* tmpls,
+                 int32_t n_tmpls, const nr_instance* inst, int64_t n_inst, double tol)
+{
+    if (nodes_allowed(P.opt, P.radix_override)) {
+        try {
+            if (build_plan(P, true, segs, n_segs, tmpls, n_tmpls, inst, n_inst, tol)) return;
+        } catch (const NrError& e) {
+            if (e.code != NR_ERR_OUT_OF_MEMORY) throw;
+        }
+        const nr_options o = P.opt;
+        P.~nr_plan_s();
+        new (&P) nr_plan_s();
+        P.opt = o;
+    }
+    build_plan(P, false, segs, n_segs, tmpls, n_tmpls, inst, n_inst, tol);
 }
 
 // ------------------------------------------------------------ execution --
@@ -1162,6 +1642,35 @@ EpilogueArgs epilogue_args(const nr_plan_s& P, const Class& c, const Chunk& ch)
 }
 
 
+NodeArgs node_args(const nr_plan_s& P, const Class& c)
+{
+    NodeArgs a{};
+    a.inst = (const InstDev*)c.d_inst.p;
+    a.coef = (const double*)c.d_coef.p;
+    a.poly = c.d_taps.p;
+    a.z = P.d_z[c.fp64].p;
+    a.dft = c.d_dft.p;
+    a.dec = c.d_dec.p;
+    a.twiddle = c.d_tw.p;
+    a.fft.n = c.n;
+    a.fft.nr = (int32_t)c.radix.size();
+    for (size_t r = 0; r < c.radix.size(); ++r) a.fft.radix[r] = c.radix[r];
+    a.count = (int64_t)c.inst.size();
+    a.row_base = c.row_base;
+    a.n = c.n;
+    a.w = c.node_w;
+    a.kmax = c.kmax;
+    a.m0max = c.kmax / 2;
+    a.strip = c.strip;
+    if (c.n <= kNodeDftMax) {
+        a.mtiles = (2 * c.kmax + 15) / 16;
+        a.ksteps = 2 * ((c.n + 3) / 4);
+        a.im_off = 4 * ((c.n + 3) / 4);
+        a.gstride = node_stride(c);
+    }
+    return a;
+}
+
 void build_groups(nr_plan_s& P)
 {
     // spread: same kernel instantiation and LDS tier
@@ -1173,14 +1682,15 @@ void build_groups(nr_plan_s& P)
     for (size_t ci = 0; ci < P.classes.size(); ++ci) {
         const Class& c = *P.classes[ci];
         if (c.inst.empty()) continue;
-        const int fused = spread_code(c.method);
+        const int fused = c.node_w ? 3 : spread_code(c.method);
         const int snap = (c.snap && !c.fp64 && c.deg <= 12) ? 1 : 0;
         // fused and separate-epilogue classes share launches (the flag is per
         // class in the launch table); their epilogue groups stay apart
         const size_t sl = spread_lds_bytes(c.fp64, c.n, c.fuse_epi && c.parts == 1);
         const std::array<int, 5> sk{c.fp64, c.deg, fused, snap, lds_tier(sl)};
         auto it = sg.find(sk);
-        if (it != sg.end() && P.spread_groups[it->second].cls.size() >= (size_t)kGroupMax) {
+        // node classes are launched one by one
+        if (it != sg.end() && (c.node_w || P.spread_groups[it->second].cls.size() >= (size_t)kGroupMax)) {
             sg.erase(it);    // full: later classes of this kind start a new group
             it = sg.end();
         }
@@ -1268,6 +1778,11 @@ void check_finite(nr_plan_s& P, const void* strain)
 // for classes whose spreader runs the epilogue (out.mode 0: grids only).
 void run_front(nr_plan_s& P, Class& c, const Chunk& ch, const EpilogueOut& out)
 {
+    if (c.node_w) {
+        timed_launch(P, NR_STAGE_SPREAD, [&] { return launch_node_spread(node_args(P, c), c.fp64, out, P.stream); },
+                     "node spread");
+        return;
+    }
     SpreadArgs a = spread_args(P, c, ch);
     if (c.method == NR_METHOD_STAGED)
         timed_launch(P, NR_STAGE_TAU, [&] { return launch_tau(a, c.fp64, P.stream); }, "tau kernel");
@@ -1285,7 +1800,8 @@ EpilogueOut spread_out(const nr_plan_s& P, EpilogueOut out, int mode)
     return out;
 }
 
-// Lane-major strain copies of every class (one launch per destination precision).
+// Lane-major strain copies of every sample class and node values of the node
+// classes (one launch per destination precision).
 void lane_major(nr_plan_s& P, const void* strain)
 {
     for (int f = 0; f < 2; ++f)
@@ -1295,6 +1811,12 @@ void lane_major(nr_plan_s& P, const void* strain)
                                                 P.lm_max_entries[f], strain, P.strain_fp64, P.opt.strain_complex,
                                                 f, P.stream);
             }, "strain layout");
+    for (int f = 0; f < 2; ++f)
+        if (P.n_filter[f])
+            timed_launch(P, NR_STAGE_LAYOUT, [&] {
+                return launch_node_filter((const FilterItem*)P.d_filter[f].p, P.n_filter[f], P.filter_lds[f],
+                                          P.d_ftaps[f].p, P.d_fwin[f].p, strain, P.d_z[f].p, P.strain_fp64, f, P.stream);
+            }, "node filter");
 }
 
 // Side streams usable for k independent launch sequences (0 when profiling:
@@ -1344,6 +1866,11 @@ void run_front_batched(nr_plan_s& P, const EpilogueOut& out)
         }
         if (g.cls.size() == 1) {
             Class& c = *P.classes[g.cls[0]];
+            if (c.node_w) {
+                timed_launch(P, NR_STAGE_SPREAD, [&] { return launch_node_spread(node_args(P, c), c.fp64, out, st); },
+                             "node spread");
+                continue;
+            }
             SpreadArgs a = spread_args(P, c, c.chunks[0]);
             timed_launch(P, NR_STAGE_SPREAD, [&] { return launch_spread(a, c.fp64, c.deg, g.fused, out, st); },
                          "spread kernel");
@@ -1910,6 +2437,23 @@ nr_status nufft_resample_query_class(nr_plan p, int32_t ci, nr_class_info* info)
         if (d.ndeg > 0) info->series_terms += (int64_t)d.L * d.ndeg;
         if (d.ndeg < 0) info->fallback_points += d.L;
     }
+    return NR_OK;
+}
+
+nr_status nufft_resample_query_nodes(nr_plan p, int32_t ci, nr_node_info* info)
+{
+    if (!p || !info || ci < 0 || ci >= (int32_t)p->classes.size()) {
+        if (p) p->err = "class index out of range";
+        return NR_ERR_INVALID_ARG;
+    }
+    const Class& c = *p->classes[ci];
+    std::memset(info, 0, sizeof(*info));
+    if (!c.node_w) return NR_OK;
+    info->width = c.node_w;
+    info->degree = 2 * node_coefs(c.node_w) - 1;
+    for (const InstDev& d : c.inst) info->nodes += d.nodes;
+    info->values = (int64_t)p->d_z[c.fp64].bytes / (c.fp64 ? 16 : 8);
+    info->filter_macs = p->filter_macs[c.fp64];
     return NR_OK;
 }
 

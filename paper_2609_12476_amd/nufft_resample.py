@@ -71,6 +71,11 @@ class NrClassInfo(ctypes.Structure):
                 ("epi_fused", c_int32), ("series_terms", c_int64), ("fallback_points", c_int64)]
 
 
+class NrNodeInfo(ctypes.Structure):
+    _fields_ = [("width", c_int32), ("degree", c_int32), ("nodes", c_int64), ("values", c_int64),
+                ("filter_macs", c_int64)]
+
+
 # symbol -> (restype, argtypes)
 SIGNATURES = {
     "nufft_resample_default_options": (None, [ctypes.POINTER(NrOptions)]),
@@ -89,6 +94,7 @@ SIGNATURES = {
     "nufft_resample_query": (c_int32, [c_void_p, ctypes.POINTER(NrPlanInfo)]),
     "nufft_resample_stage_times": (c_int32, [c_void_p, ctypes.POINTER(NrStageTimes)]),
     "nufft_resample_query_class": (c_int32, [c_void_p, c_int32, ctypes.POINTER(NrClassInfo)]),
+    "nufft_resample_query_nodes": (c_int32, [c_void_p, c_int32, ctypes.POINTER(NrNodeInfo)]),
     "nufft_resample_bin_offsets": (c_int32, [c_void_p, c_void_p]),
     "nufft_resample_stat_offsets": (c_int32, [c_void_p, c_void_p]),
     "nufft_resample_valid_mask": (c_int32, [c_void_p, c_void_p]),
@@ -182,6 +188,12 @@ def nufft_resample_stage_times(plan):
 def nufft_resample_query_class(plan, c):
     info = NrClassInfo()
     _check(load().nufft_resample_query_class(plan, c, ctypes.byref(info)), plan)
+    return info
+
+
+def nufft_resample_query_nodes(plan, c):
+    info = NrNodeInfo()
+    _check(load().nufft_resample_query_nodes(plan, c, ctypes.byref(info)), plan)
     return info
 
 
@@ -338,6 +350,10 @@ class Plan:
     # -- host-side descriptions ------------------------------------------------
     def classes(self):
         return [nufft_resample_query_class(self.handle, c) for c in range(self.info.n_classes)]
+
+    def nodes(self):
+        """Band-limited nodes of every class (width 0: the class reads samples)."""
+        return [nufft_resample_query_nodes(self.handle, c) for c in range(self.info.n_classes)]
 
     def bin_offsets(self):
         return nufft_resample_bin_offsets(self.handle, self.n_inst)

@@ -1,0 +1,137 @@
+"""The band-limited node path against the oracle, at the sizes where it can go
+wrong: the smallest and largest small grid, a grid past it (FFT), node counts
+off the multiples of a wave, nodes closer than a cell and further apart, bands
+that sweep, reference frequencies over several tiles, odd rates and lengths.
+
+Bounds: an instance's relative l2 error is at most its tolerance plus the FP32
+rounding of the spectra (1e-6); FP64 down to the phase's own error (2 pi times
+the cycles times a few 2^-53: under 5e-12 here)."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def workload(seed, n_seg, L, fs, n_mc, subs, K, df, f_max=0.0, mcs=None, t0=0.0):
+    """n_seg segments x n_mc chirp masses x the sub-bands starting at subs, K bins of df."""
+    rng = np.random.default_rng(seed)
+    off, ln, fsa, ts = synth._segments(n_seg, L, fs)
+    mc = synth.log_spaced_mc(n_mc) if mcs is None else np.asarray(mcs, float)
+    m, b = np.repeat(mc, len(subs)), np.tile(np.asarray(subs, float), len(mc))
+    n = len(m)
+    return synth.Workload(
+        name="nodes", strain=rng.standard_normal(n_seg * L).astype(np.float32).astype(np.float64), seg_offset=off,
+        seg_len=ln, seg_fs=fsa, seg_t=ts + t0, mc=m, f0=b + 0.5 * K * df, f_lo=b, df=np.full(n, df),
+        n_bins=np.full(n, K, np.int32), f_max=np.full(n, f_max), tol=1e-6)
+
+
+SHAPES = {
+    # name: segments, samples, rate, masses, sub-bands, bins, bin spacing, further arguments
+    "search": (3, 7680, 256.0, 24, (40, 41, 59), 30, 1 / 30, dict(f_max=62.0)),
+    "sweep": (3, 7680, 256.0, 24, (45, 47), 30, 1 / 30, dict(mcs=np.geomspace(0.05, 0.1, 24), t0=600.0, f_max=62.0)),
+    "many_refs": (2, 7680, 256.0, 12, tuple(range(20, 64)), 30, 1 / 30, {}),
+    "largest_small_grid": (2, 16384, 256.0, 48, (40, 50), 64, 1 / 64, {}),
+    "first_fft_grid": (2, 16640, 256.0, 48, (40, 50), 65, 1 / 65, {}),
+    "band": (2, 15360, 512.0, 69, (40,), 600, 1 / 30, {}),
+    "few_bins": (3, 4097, 200.0, 64, (30, 33), 5, 0.2, {}),
+    "one_bin": (2, 5003, 128.0, 64, (33,), 1, 0.1, {}),
+    "coarse_bins": (2, 3001, 512.0, 128, (40,), 8, 0.5, {}),
+    "identity": (2, 7680, 256.0, 64, (40,), 30, 1 / 30, dict(mcs=np.zeros(64))),
+    "high_rate": (2, 30000, 1000.0, 32, (40, 44), 30, 1 / 30, {}),
+    "negative": (2, 7680, 256.0, 64, (-3,), 30, 1 / 30, dict(mcs=np.zeros(64))),
+}
+
+
+@pytest.mark.parametrize("prec,tol", [("fp32", 1e-6), ("fp32", 1e-4), ("fp64", 1e-9), ("fp64", 1e-12)])
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_nodes_match_oracle(gpu, name, prec, tol):
+    import torch
+    from paper_2609_12476_amd import Plan, complex_view
+    print(f"nodes {name} {prec} {tol}", flush=True)
+    *args, kw = SHAPES[name]
+    w = workload(11, *args, **kw)
+    with Plan.from_workload(w, precision=prec, tol=tol) as p, \
+            Plan.from_workload(w, precision=prec, tol=tol, method="cellrun") as q:
+        nodes = p.nodes()
+        assert any(c.width for c in nodes), "the node path was not taken"
+        assert all(c.width == 0 for c in q.nodes())
+        x = p.strain_tensor(w.strain, gpu)
+        sp, pw, valid = p.execute(x)
+        stat, used = p.semicoherent_sum(x)
+        stat2, used2 = p.semicoherent_sum(x)
+        sq, uq = q.semicoherent_sum(x)
+        torch.cuda.synchronize()
+        X, P = complex_view(sp).cpu().numpy().astype(np.complex128), pw.cpu().numpy().astype(np.float64)
+        off, ok = p.bin_offsets(), p.valid_mask().astype(bool)
+        assert np.array_equal(valid.cpu().numpy().astype(bool), ok) and np.array_equal(q.valid_mask().astype(bool), ok)
+        soff = p.stat_offsets()
+    assert torch.equal(stat, stat2) and torch.equal(used, used2) and torch.equal(used, uq)
+    idx = np.flatnonzero(ok)
+    idx = np.unique(np.concatenate([idx[:3], idx[-3:], np.random.default_rng(3).choice(idx, min(len(idx), 18), False)]))
+    Xr, roff, okr = oracle.spectra(w, inst_idx=idx)
+    assert okr.all()
+    bound = tol + 1e-6 if prec == "fp32" else max(tol, 5e-12)
+    errs = [np.linalg.norm(X[off[i]:off[i + 1]] - Xr[roff[j]:roff[j + 1]]) / np.linalg.norm(Xr[roff[j]:roff[j + 1]])
+            for j, i in enumerate(idx)]
+    print(f"  {len(idx)} instances, worst {max(errs):.2e}, nodes {[c.nodes for c in nodes]}", flush=True)
+    assert max(errs) <= bound
+    np.testing.assert_allclose(P, np.abs(X) ** 2, rtol=1e-5 if prec == "fp32" else 1e-13, atol=0)
+    for i in np.flatnonzero(~ok):
+        assert not X[off[i]:off[i + 1]].any()
+    # the sums: twice an instance's amplitude error, against the sample path's
+    for m in range(len(soff) - 1):
+        a, b = (t.cpu().numpy().astype(np.float64)[soff[m]:soff[m + 1]] for t in (stat, sq))
+        assert np.linalg.norm(a - b) <= 4.0 * bound * np.linalg.norm(b)
+
+
+def test_auto_precision_and_weights(gpu):
+    """Mixed tolerances (FP32 and FP64 node classes beside sample classes) over double strain."""
+    import torch
+    from paper_2609_12476_amd import Plan, complex_view
+    w = workload(5, 4, 7680, 256.0, 48, (40, 44, 52), 30, 1 / 30, f_max=62.0)
+    s, m = w.instances()
+    tols = np.array([1e-3, 1e-6, 1e-9])[m % 3]
+    w.inst_seg, w.inst_tmpl, w.inst_tol = s, m, tols
+    wt = np.array([1.0, 0.5, 0.0, 2.0])
+    with Plan.from_workload(w, precision="auto") as p:
+        widths = [c.width for c in p.nodes()]
+        assert 8 in widths and 12 in widths and 0 in widths
+        x = p.strain_tensor(w.strain, gpu)
+        sp, _, valid = p.execute(x)
+        stat, used = p.semicoherent_sum(x, torch.tensor(wt, device=gpu))
+        torch.cuda.synchronize()
+        X, off = complex_view(sp).cpu().numpy(), p.bin_offsets()
+        S, soff, U = stat.cpu().numpy(), p.stat_offsets(), used.cpu().numpy()
+    idx = np.flatnonzero(valid.cpu().numpy())[::9]
+    Xr, roff, _ = oracle.spectra(w, inst_idx=idx)
+    for j, i in enumerate(idx):
+        a, b = X[off[i]:off[i + 1]], Xr[roff[j]:roff[j + 1]]
+        assert np.linalg.norm(a - b) <= (tols[i] + (1e-6 if tols[i] >= 1e-6 else 0.0)) * np.linalg.norm(b)
+    for t in range(0, w.n_tmpl, 7):
+        i = np.flatnonzero(m == t)
+        ref = sum(wt[s[q]] * np.abs(X[off[q]:off[q + 1]]) ** 2 for q in i if valid[q])
+        np.testing.assert_allclose(S[soff[t]:soff[t + 1]], ref, rtol=1e-12)
+        assert U[t] == sum(int(valid[q]) for q in i)
+
+
+@pytest.mark.parametrize("kw", [dict(method="cellrun"), dict(parts=2), dict(epilogue="separate"), dict(sigma=2.5),
+                                dict(flush_period=8), dict(moment_mode=1), dict(max_workspace_bytes=200_000)])
+def test_options_keep_the_sample_path(gpu, kw):
+    """Options that pick a spreader keep the samples, and so does a workspace that holds the
+    sample path's strain copy (61 kB) and a chunk of grids but not every instance's power
+    row (245 kB), which the node path needs."""
+    import torch
+    from paper_2609_12476_amd import Plan
+    w = workload(7, 2, 7680, 256.0, 512, (40, 41), 30, 1 / 30)
+    with Plan.from_workload(w, precision="fp32", tol=1e-6, **kw) as p, \
+            Plan.from_workload(w, precision="fp32", tol=1e-6) as q:
+        assert all(c.width == 0 for c in p.nodes()) and any(c.width for c in q.nodes())
+        x = p.strain_tensor(w.strain, gpu)
+        a, ua = p.semicoherent_sum(x)
+        b, ub = q.semicoherent_sum(x)
+        torch.cuda.synchronize()
+    assert torch.equal(ua, ub)
+    assert torch.linalg.norm(a.double() - b.double()) <= 1e-5 * torch.linalg.norm(b.double())
