@@ -153,10 +153,8 @@ constexpr int kNodeDftMax = 128;   // largest grid transformed by the small DFT
 // Row of accumulator i of the lanes l / 16 = g in a 16 x 16 matrix product.
 __host__ __device__ inline int mfma_row(bool fp64, int g, int i) { return fp64 ? 4 * i + g : 4 * g + i; }
 
-// Images of the filter's window folded onto one period of the carriers, by
-// precision (odd; the window's half-width is at most (images / 2 + 1/2) periods).
-constexpr int kImages32 = 5, kImages64 = 9;
-constexpr int kFilterTiles = 2;    // tiles of one filter workgroup at most
+// Tiles of one filter workgroup at most: in FP64 four would leave one wave per SIMD.
+constexpr int filter_tiles(bool fp64) { return fp64 ? 2 : 4; }
 
 // Work of one filter workgroup: nodes node0 .. node0 + 63 of one segment for
 // `tiles` consecutive tiles of 16 reference frequencies.
@@ -164,7 +162,7 @@ struct FilterItem {
     int64_t src_off;    // first sample of the segment in the caller's strain
     int64_t z_off;      // node values of the first frequency ([16 tiles][nodes])
     int64_t tap_off;    // carriers of the first tile: per tile [4 ksteps][64 lanes] (cosine, -sine) pairs
-    int64_t win_off;    // window [16 ksteps][images, padded to four]
+    int64_t win_off;    // window [16 ksteps][images of k, padded to four]
     int32_t L;          // samples
     int32_t D;          // samples between nodes
     int32_t Q;          // period of the carriers in samples
@@ -204,8 +202,16 @@ inline size_t node_fft_lds_bytes(int fp64, int n, int strip)
     return (size_t)(n + (4 * strip > n ? 4 * strip : n)) * (fp64 ? 16 : 8);
 }
 size_t filter_lds_bytes(int fp64, int D, int Q, int ksteps, int images);
-hipError_t launch_node_filter(const FilterItem* items, int64_t count, size_t lds, const void* carriers,
-                              const void* window, const void* strain, void* z, int strain_fp64, int fp64,
+struct FilterLaunch {
+    const FilterItem* items;
+    int64_t count;
+    int32_t tiles;           // the most tiles of any item
+    int32_t images;          // images of the window on one period of the carriers: 5; FP64 7 or 9
+    size_t lds;
+    const void* carriers;
+    const void* window;
+};
+hipError_t launch_node_filter(const FilterLaunch& f, const void* strain, void* z, int strain_fp64, int fp64,
                               hipStream_t st);
 
 // Launch wrappers (defined in nr_kernels.hip).

@@ -71,12 +71,16 @@ struct Mfma<double> {
 // One workgroup: 64 consecutive nodes (16 per wave) of one segment, MT tiles.
 // Node windows overlap, so the samples are staged in LDS once and each lane
 // folds the B values of its (k, node) itself, for all MT tiles: 2 I reads and
-// 4 I operations beside 2 MT matrix steps.  D = 4 (mod 8) spreads the lanes'
-// reads (node stride D, four consecutive k) over all banks.  In FP32 four chains
+// 4 I operations beside 2 MT matrix steps.  A group of lanes whose read the
+// 32 banks serve together (32 lanes in FP32: 16 nodes, two k; 16 in FP64)
+// finds distinct banks for D = 2 (mod 4) in FP32 and odd D in FP64.  In FP32 four chains
 // per product keep the rounding of the FP32 sums below that of the spreading.
-// Measured on the 1 h workload (120 segments of 7680 samples, 41 carriers at
-// 121 and 29 at 243 nodes): 44 us, against 106 us for a product of the
-// unfolded taps (1260 instead of 253 contraction steps per product).
+// Measured on the 1 h workload (120 segments of 7680 samples; 45 carriers at
+// 128 nodes, 26 at 250): 106 us for a product of the unfolded taps (1260
+// instead of 235 contraction steps per product), 44 us folded with two tiles a
+// workgroup and node spacings of 4 (mod 8), whose reads met on half the banks,
+// 35 us with up to four tiles, 29 us free of bank conflicts (the latency of
+// 11 us of matrix steps at two waves a SIMD); beta bank 31 -> 20 us.
 template <typename T, typename Ti, int MT, int I>
 __device__ __forceinline__ void node_filter_block(const FilterItem& it, const Ti* __restrict__ strain,
                                                   const T* __restrict__ carriers, const T* __restrict__ window,
@@ -91,16 +95,16 @@ __device__ __forceinline__ void node_filter_block(const FilterItem& it, const Ti
     const int64_t w0 = (int64_t)it.j0 + (int64_t)it.node0 * D - reach;
     const int len = (kNodeTile - 1) * D + 2 * reach + 1;
     const Ti* __restrict__ src = strain + it.src_off;
-    // eight loads in flight per thread
-    for (int q0 = threadIdx.x; q0 < len; q0 += 8 * kBlock) {
-        Ti v[8];
+    // 16 loads in flight per thread
+    for (int q0 = threadIdx.x; q0 < len; q0 += 16 * kBlock) {
+        Ti v[16];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < 16; ++u) {
             const int64_t j = w0 + q0 + u * kBlock;
             v[u] = q0 + u * kBlock < len && j >= 0 && j < it.L ? src[j] : Ti(0);
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
+        for (int u = 0; u < 16; ++u)
             if (q0 + u * kBlock < len) xs[q0 + u * kBlock] = (T)v[u];
     }
     for (int q0 = threadIdx.x; q0 < kp * IS; q0 += 8 * kBlock) {
@@ -121,7 +125,7 @@ __device__ __forceinline__ void node_filter_block(const FilterItem& it, const Ti
     using V2 = cpx<T>;                                       // (cosine, -sine) of a lane
     const V2* __restrict__ tp = reinterpret_cast<const V2*>(carriers) + it.tap_off + lane;
     const int64_t tile = (int64_t)it.ksteps * 4 * 64;
-    constexpr int CH = sizeof(T) == 4 ? 4 : 1;                // chains
+    constexpr int CH = sizeof(T) == 8 ? 1 : MT <= 2 ? 4 : 2;  // chains
     typename Mfma<T>::acc re[MT][CH], im[MT][CH];
 #pragma unroll
     for (int t = 0; t < MT; ++t)
@@ -171,6 +175,10 @@ __device__ __forceinline__ void node_filter_block(const FilterItem& it, const Ti
         for (int i = 0; i < 4; ++i) {
             const int f = kFilterRows * t + mfma_row(sizeof(T) == 8, kq, i);
             T r = re[t][0][i], q = im[t][0][i];
+            if constexpr (CH == 2) {
+                r += re[t][1][i];
+                q += im[t][1][i];
+            }
             if constexpr (CH == 4) {
                 r = (r + re[t][1][i]) + (re[t][2][i] + re[t][3][i]);
                 q = (q + im[t][1][i]) + (im[t][2][i] + im[t][3][i]);
@@ -179,7 +187,9 @@ __device__ __forceinline__ void node_filter_block(const FilterItem& it, const Ti
         }
 }
 
-template <typename T, typename Ti, int I>
+// MAXT: the most tiles of any item of the launch (its registers set the
+// kernel's occupancy: 16 accumulators a tile in FP32).
+template <typename T, typename Ti, int I, int MAXT>
 __global__ __launch_bounds__(kBlock) void node_filter_kernel(const FilterItem* __restrict__ items,
                                                              const Ti* __restrict__ strain,
                                                              const T* __restrict__ carriers,
@@ -188,10 +198,15 @@ __global__ __launch_bounds__(kBlock) void node_filter_kernel(const FilterItem* _
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T* lds = reinterpret_cast<T*>(smem_raw);
     const FilterItem it = items[blockIdx.x];
-    if (uniform(it.tiles) == 1)
+    const int tiles = uniform(it.tiles);
+    if (MAXT == 1 || tiles == 1)
         node_filter_block<T, Ti, 1, I>(it, strain, carriers, window, z, lds);
+    else if (MAXT == 2 || tiles == 2)
+        node_filter_block<T, Ti, 2, I>(it, strain, carriers, window, z, lds);
+    else if (tiles == 3)
+        node_filter_block<T, Ti, 3, I>(it, strain, carriers, window, z, lds);
     else
-        node_filter_block<T, Ti, kFilterTiles, I>(it, strain, carriers, window, z, lds);
+        node_filter_block<T, Ti, 4, I>(it, strain, carriers, window, z, lds);
 }
 
 // ---------------------------------------------------------------- spread --
@@ -207,16 +222,18 @@ __device__ __forceinline__ const NR_CONST X* as_const(const X* p)
     return (const NR_CONST X*)(uintptr_t)p;
 }
 
-__device__ __forceinline__ InstDev load_inst(const InstDev* p)
+// A record of whole 64-bit words at a wave-uniform address.
+template <typename X>
+__device__ __forceinline__ X load_const(const NR_CONST void* p)
 {
-    static_assert(sizeof(InstDev) == 96, "twelve words");
-    const NR_CONST uint64_t* q = (const NR_CONST uint64_t*)(uintptr_t)p;
-    uint64_t w[12];
+    static_assert(sizeof(X) % 8 == 0 && alignof(X) <= 8, "whole words");
+    const NR_CONST uint64_t* q = (const NR_CONST uint64_t*)p;
+    uint64_t w[sizeof(X) / 8];
 #pragma unroll
-    for (int i = 0; i < 12; ++i) w[i] = q[i];
-    InstDev d;
-    __builtin_memcpy(&d, w, sizeof d);
-    return d;
+    for (size_t i = 0; i < sizeof(X) / 8; ++i) w[i] = q[i];
+    X x;
+    __builtin_memcpy(&x, w, sizeof x);
+    return x;
 }
 
 // dtau at NP sample positions (series of dtau_of, uniform degree).
@@ -294,27 +311,80 @@ struct Cell<double> {
     typedef double v __attribute__((ext_vector_type(2)));
 };
 
-// The W tap values of a node.  u = 1 - 2 frac(S) in (-1, 1]; tap t is
-// E_t(u^2) + u O_t(u^2) and, the kernel being even, tap W - 1 - t is E_t(u^2)
-// - u O_t(u^2): half the polynomial work.  poly: per pair t < W / 2 the NE
-// even coefficients, then the NE odd ones (W even).
+// Coefficients of the kernel pieces: per pair t < W / 2 the NE even, then the
+// NE odd ones, read over the scalar cache; in FP32 the leading ones stay in
+// vector registers (an fma reads one scalar operand only).
 template <typename T, int W, int NE>
-__device__ __forceinline__ void node_taps(const NR_CONST T* poly, T u, T* a)
+struct NodePoly;
+template <int W, int NE>
+struct NodePoly<float, W, NE> {
+    const NR_CONST float* q;
+    float lead[W];
+    __device__ __forceinline__ void load(const void* p)
+    {
+        q = as_const(reinterpret_cast<const float*>(p));
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            lead[k] = q[k * NE + NE - 1];
+            asm volatile("" : "+v"(lead[k]));
+        }
+    }
+    __device__ __forceinline__ float top(int h) const { return lead[h]; }
+    __device__ __forceinline__ float at(int h, int k) const { return q[h * NE + k]; }
+    static __device__ __forceinline__ void fence() {}
+};
+template <int W, int NE>
+struct NodePoly<double, W, NE> {
+    const NR_CONST double* q;
+    __device__ __forceinline__ void load(const void* p) { q = as_const(reinterpret_cast<const double*>(p)); }
+    __device__ __forceinline__ double top(int h) const { return q[h * NE + NE - 1]; }
+    __device__ __forceinline__ double at(int h, int k) const { return q[h * NE + k]; }
+    // a pair's coefficients are not fetched before the last pair's are used up
+    static __device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
+};
+
+// The W tap values of NP nodes.  u = 1 - 2 frac(S) in (-1, 1]; tap t is
+// E_t(u^2) + u O_t(u^2) and, the kernel being even, tap W - 1 - t is E_t(u^2)
+// - u O_t(u^2): half the polynomial work (W even).
+template <typename T, int W, int NE, int NP>
+__device__ __forceinline__ void node_taps(const NodePoly<T, W, NE>& poly, const T* u, T (*a)[W])
 {
-    const T u2 = u * u;
+    T u2[NP];
+#pragma unroll
+    for (int e = 0; e < NP; ++e) u2[e] = u[e] * u[e];
 #pragma unroll
     for (int t = 0; t < W / 2; ++t) {
-        const NR_CONST T* pe = poly + t * 2 * NE;
-        T ev = pe[NE - 1], od = pe[2 * NE - 1];
+        T ev[NP], od[NP];
 #pragma unroll
-        for (int k = NE - 2; k >= 0; --k) {
-            ev = fma(ev, u2, pe[k]);
-            od = fma(od, u2, pe[NE + k]);
+        for (int e = 0; e < NP; ++e) {
+            ev[e] = fma(poly.top(2 * t), u2[e], poly.at(2 * t, NE - 2));
+            od[e] = fma(poly.top(2 * t + 1), u2[e], poly.at(2 * t + 1, NE - 2));
         }
-        a[t] = fma(u, od, ev);
-        a[W - 1 - t] = fma(-u, od, ev);
+#pragma unroll
+        for (int k = NE - 3; k >= 0; --k)
+#pragma unroll
+            for (int e = 0; e < NP; ++e) {
+                ev[e] = fma(ev[e], u2[e], poly.at(2 * t, k));
+                od[e] = fma(od[e], u2[e], poly.at(2 * t + 1, k));
+            }
+#pragma unroll
+        for (int e = 0; e < NP; ++e) {
+            a[e][t] = fma(u[e], od[e], ev[e]);
+            a[e][W - 1 - t] = fma(-u[e], od[e], ev[e]);
+        }
+        poly.fence();
     }
 }
+
+// Two consecutive node values (a row's values are aligned to one value only).
+template <typename T>
+struct alignas(sizeof(T) * 2) NodePairHalf {
+    T x, y;
+};
+template <typename T>
+struct NodeValues {
+    NodePairHalf<T> v[2];
+};
 
 // The nodes [first, first + count) of an instance onto the wave's strip of
 // unwrapped cells; lane v takes nodes v * stride + r of them, r < stride.
@@ -327,67 +397,63 @@ __device__ __forceinline__ void node_taps(const NR_CONST T* poly, T u, T* a)
 // less than a cell apart (pair), a lane's two nodes share W + 1 cells and
 // their taps are summed in registers: 9 instead of 16 cell updates (W = 8).
 // 1 h workload, 122,501 instances of about 121 nodes: 1430 us per step with
-// LDS additions, 123 us with updates tap by tap, 94 us with the pairs (0.64 of
-// the VALU's issue, the rest the chain of updates); its sample spreader, the
+// LDS additions, 123 us with updates tap by tap, 94 us with the pairs, 88 us
+// with node pairs loaded and placed together (273 VALU instructions an
+// instance, 0.7 of their issue at the clock it runs at; the rest is the chain
+// of updates and the scalar loads before it); its sample spreader, the
 // cell-run kernel, takes 1240 us.
 template <typename T, int W, int NE>
-__device__ __forceinline__ int node_strip(const InstDev& d, const NodeArgs& a, int first, int count, int lane,
-                                          typename Cell<T>::v* strip)
+__device__ __forceinline__ int node_strip(const InstDev& d, const NodeArgs& a, const NodePoly<T, W, NE>& poly,
+                                          int first, int count, int lane, typename Cell<T>::v* strip)
 {
     using V = typename Cell<T>::v;
     const NR_CONST double* coef = as_const(a.coef + d.coef_off);
     const cpx<T>* __restrict__ z = reinterpret_cast<const cpx<T>*>(a.z) + d.strain_off + first;
-    const NR_CONST T* poly = as_const(reinterpret_cast<const T*>(a.poly));
     const double dfn = d.df * (double)a.n, hnn = 0.5 * (double)W;
-    const int j0 = (int)d.pt_off + first * d.C;
-    const int hi = (int)(d.pt_off >> 32);
+    const double j0 = (double)(uniform((int)d.pt_off) + first * d.C), Cd = (double)d.C;
+    const int hi = uniform((int)(d.pt_off >> 32));
     const int apart = (hi & 0xffff) + 1;            // lanes' nodes at least a cell apart
-    const bool pair = (hi >> 16) != 0;
+    const bool pair = hi > 0xffff;
     const int need = (count + kWave - 1) / kWave;
     const int stride = need > apart ? need : apart;
     int base = 0;
     for (int r0 = 0; r0 < stride; r0 += 2) {
+        // nodes b and b + 1 of the lane; past the instance's last node the
+        // values are dropped (the row's end is followed by a spare value)
+        const int b = __mul24(lane, stride) + r0;
+        const bool on0 = b < count, on1 = r0 + 1 < stride && b + 1 < count;
+        NodeValues<T> zv = *reinterpret_cast<const NodeValues<T>*>(z + (on0 ? b : 0));
         double x[2], dt[2];
-        cpx<T> zv[2];
-        bool on[2];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int b = lane * stride + r0 + e;
-            on[e] = r0 + e < stride && b < count;
-            const int bc = on[e] ? b : 0;
-            zv[e] = z[bc];
-            x[e] = (double)(j0 + bc * d.C);
-        }
+        x[0] = fma((double)b, Cd, j0);
+        x[1] = x[0] + Cd;
         node_dtau<2>(d.ndeg, d.c, coef, x, dt);
         int g[2];
-        T u[2];
+        T u[2], ta[2][W];
         cpx<T> c[2];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const double S = fma(dfn, dt[e], -hnn), fl = floor(S);
             g[e] = (int)fl;
             u[e] = (T)fma(-2.0, S - fl, 1.0);
-            c[e] = node_heterodyne(d.fc * dt[e], zv[e]);
+            c[e] = node_heterodyne(d.fc * dt[e], cpx<T>{zv.v[e].x, zv.v[e].y});
         }
         if (r0 == 0) base = uniform(g[0]);
-        if (on[0]) {
+        if (on0) {
             V* cells = strip + (g[0] - base);
-            T ta[W], tb[W];
-            node_taps<T, W, NE>(poly, u[0], ta);
-            node_taps<T, W, NE>(poly, u[1], tb);
+            node_taps<T, W, NE, 2>(poly, u, ta);
             if (pair) {
-                if (!on[1]) c[1] = cpx<T>{T(0), T(0)};
-                const bool same = !on[1] || g[1] == g[0];
+                if (!on1) c[1] = cpx<T>{T(0), T(0)};
+                const bool same = !on1 || g[1] == g[0];
 #pragma unroll
                 for (int t = 0; t <= W; ++t) {
-                    const T b = same ? (t < W ? tb[t < W ? t : 0] : T(0)) : (t > 0 ? tb[t > 0 ? t - 1 : 0] : T(0));
+                    const T q = same ? (t < W ? ta[1][t < W ? t : 0] : T(0)) : (t > 0 ? ta[1][t > 0 ? t - 1 : 0] : T(0));
                     V v = cells[t];
                     if (t < W) {
-                        v.x = fma(ta[t < W ? t : 0], c[0].x, v.x);
-                        v.y = fma(ta[t < W ? t : 0], c[0].y, v.y);
+                        v.x = fma(ta[0][t < W ? t : 0], c[0].x, v.x);
+                        v.y = fma(ta[0][t < W ? t : 0], c[0].y, v.y);
                     }
-                    v.x = fma(b, c[1].x, v.x);
-                    v.y = fma(b, c[1].y, v.y);
+                    v.x = fma(q, c[1].x, v.x);
+                    v.y = fma(q, c[1].y, v.y);
                     cells[t] = v;
                     lane_order();
                 }
@@ -395,23 +461,22 @@ __device__ __forceinline__ int node_strip(const InstDev& d, const NodeArgs& a, i
 #pragma unroll
                 for (int t = 0; t < W; ++t) {
                     V v = cells[t];
-                    v.x = fma(ta[t], c[0].x, v.x);
-                    v.y = fma(ta[t], c[0].y, v.y);
+                    v.x = fma(ta[0][t], c[0].x, v.x);
+                    v.y = fma(ta[0][t], c[0].y, v.y);
                     cells[t] = v;
                     lane_order();
                 }
             }
         }
         lane_order();
-        if (!pair && on[1]) {
+        if (!pair && on1) {
             V* cells = strip + (g[1] - base);
-            T tb[W];
-            node_taps<T, W, NE>(poly, u[1], tb);
+            node_taps<T, W, NE, 1>(poly, u + 1, ta + 1);
 #pragma unroll
             for (int t = 0; t < W; ++t) {
                 V v = cells[t];
-                v.x = fma(tb[t], c[1].x, v.x);
-                v.y = fma(tb[t], c[1].y, v.y);
+                v.x = fma(ta[1][t], c[1].x, v.x);
+                v.y = fma(ta[1][t], c[1].y, v.y);
                 cells[t] = v;
                 lane_order();
             }
@@ -473,36 +538,53 @@ __device__ __forceinline__ cpx<T> node_fold(const V* strip, int base, int len, i
 // transforms the 16 grids at once: X = F G with F [2 K][2 n] the DFT of the
 // wanted modes with the deconvolution in its rows, a 16-column matrix product.
 template <typename T, int W, int NE>
-__global__ __launch_bounds__(kBlock) void node_spread_dft_kernel(NodeArgs a, EpilogueOut o)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 8 : 1))) void
+node_spread_dft_kernel(NodeArgs a0, EpilogueOut o0)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T* lds = reinterpret_cast<T*>(smem_raw);
     const int wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int n = a.n, gs = a.gstride, imo = a.im_off;
     const int64_t item0 = (int64_t)blockIdx.x * kNodeBatch;
-    for (int q = threadIdx.x; q < kNodeBatch * gs; q += kBlock) lds[q] = T(0);
-    __syncthreads();
+    {
+        const int n = a0.n, gs = a0.gstride, imo = a0.im_off;
+        uint4* words = reinterpret_cast<uint4*>(smem_raw);
+        for (int q = threadIdx.x; q < kNodeBatch * gs * (int)sizeof(T) / 16; q += kBlock) words[q] = uint4{0, 0, 0, 0};
+        NodePoly<T, W, NE> poly;
+        poly.load(a0.poly);
+        __syncthreads();
 #pragma unroll 1
-    for (int q = 0; q < kNodeBatch / 4; ++q) {
-        const int64_t item = item0 + wave * (kNodeBatch / 4) + q;
-        if (item >= a.count) break;
-        const InstDev d = load_inst(a.inst + item);
-        T* grid = lds + (wave * (kNodeBatch / 4) + q) * gs;
-        auto* strip = reinterpret_cast<typename Cell<T>::v*>(grid);
-        const int base = floor_mod(node_strip<T, W, NE>(d, a, 0, d.nodes, lane, strip), n);
-        cpx<T> v[kNodeDftMax / kWave];
+        for (int q = 0; q < kNodeBatch / 4; ++q) {
+            const int64_t item = item0 + wave * (kNodeBatch / 4) + q;
+            if (item >= a0.count) break;
+            const InstDev d = load_const<InstDev>(as_const(a0.inst + item));
+            T* grid = lds + (wave * (kNodeBatch / 4) + q) * gs;
+            auto* strip = reinterpret_cast<typename Cell<T>::v*>(grid);
+            const int base = floor_mod(node_strip<T, W, NE>(d, a0, poly, 0, d.nodes, lane, strip), n);
+            cpx<T> v[kNodeDftMax / kWave];
 #pragma unroll
-        for (int e = 0; e < kNodeDftMax / kWave; ++e)
-            if (lane + e * kWave < n) v[e] = node_fold<T>(strip, base, a.strip, lane + e * kWave, n);
-        lane_order();
+            for (int e = 0; e < kNodeDftMax / kWave; ++e)
+                if (lane + e * kWave < n) v[e] = node_fold<T>(strip, base, a0.strip, lane + e * kWave, n);
+            lane_order();
 #pragma unroll
-        for (int e = 0; e < kNodeDftMax / kWave; ++e)
-            if (lane + e * kWave < n) {
-                grid[lane + e * kWave] = v[e].x;
-                grid[imo + lane + e * kWave] = v[e].y;
-            }
+            for (int e = 0; e < kNodeDftMax / kWave; ++e)
+                if (lane + e * kWave < n) {
+                    grid[lane + e * kWave] = v[e].x;
+                    grid[imo + lane + e * kWave] = v[e].y;
+                }
+        }
     }
     __syncthreads();
+    // FP32: the arguments once more, from where the kernel got them (kept in
+    // scalar registers across the spreading they would spill)
+    NodeArgs a = a0;
+    EpilogueOut o = o0;
+    if constexpr (sizeof(T) == 4) {
+        const NR_CONST char* args = (const NR_CONST char*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));
+        a = load_const<NodeArgs>(args);
+        o = load_const<EpilogueOut>(args + sizeof(NodeArgs));
+    }
+    const int gs = a.gstride, imo = a.im_off;
     const int nn = lane & 15, kq = lane >> 4;
     const T* __restrict__ col = lds + nn * gs + kq;
     const int half = a.ksteps / 2;
@@ -510,9 +592,18 @@ __global__ __launch_bounds__(kBlock) void node_spread_dft_kernel(NodeArgs a, Epi
     for (int tile = wave; tile < a.mtiles; tile += 4) {
         const T* __restrict__ A = reinterpret_cast<const T*>(a.dft) + (int64_t)tile * a.ksteps * 64 + lane;
         typename Mfma<T>::acc c0{}, c1{};
-        for (int ks = 0; ks < half; ++ks) {
-            c0 = Mfma<T>::step(A[ks * 64], col[4 * ks], c0);
-            c1 = Mfma<T>::step(A[(half + ks) * 64], col[imo + 4 * ks], c1);
+        for (int ks = 0; ks < half; ks += 4) {
+            T ar[4], ai[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                ar[e] = A[(ks + e) * 64];
+                ai[e] = A[(half + ks + e) * 64];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                c0 = Mfma<T>::step(ar[e], col[4 * (ks + e)], c0);
+                c1 = Mfma<T>::step(ai[e], col[imo + 4 * (ks + e)], c1);
+            }
         }
         if (item >= a.count) continue;
         const InstDev* __restrict__ d = a.inst + item;
@@ -544,11 +635,13 @@ __global__ __launch_bounds__(kBlock) void node_spread_fft_kernel(NodeArgs a, Epi
     const int64_t item = blockIdx.x;
     for (int q = threadIdx.x; q < 4 * len; q += kBlock) strips[q] = V{T(0), T(0)};
     __syncthreads();
-    const InstDev d = load_inst(a.inst + item);
+    const InstDev d = load_const<InstDev>(as_const(a.inst + item));
     const int per = (d.nodes + 3) / 4, first = wave * per;
     const int count = d.nodes - first < per ? d.nodes - first : per;
     int base = 0;
-    if (count > 0) base = node_strip<T, W, NE>(d, a, first, count, lane, strips + wave * len);
+    NodePoly<T, W, NE> poly;
+    poly.load(a.poly);
+    if (count > 0) base = node_strip<T, W, NE>(d, a, poly, first, count, lane, strips + wave * len);
     if (lane == 0) bases[wave] = floor_mod(base, n);
     __syncthreads();
     for (int c = threadIdx.x; c < n; c += kBlock) {
@@ -580,25 +673,35 @@ size_t filter_lds_bytes(int fp64, int D, int Q, int ksteps, int images)
     return (size_t)((kNodeTile - 1) * D + 2 * reach + 1 + kp * ((images + 3) / 4 * 4)) * (fp64 ? 8 : 4);
 }
 
-template <typename T, typename Ti, int I>
-static hipError_t launch_node_filter_k(const FilterItem* items, int64_t count, size_t lds, const void* carriers,
-                                       const void* window, const void* strain, void* z, hipStream_t st)
+template <typename T, typename Ti, int I, int MAXT>
+static hipError_t launch_node_filter_k(const FilterLaunch& f, const void* strain, void* z, hipStream_t st)
 {
-    allow_lds(node_filter_kernel<T, Ti, I>, lds);
-    node_filter_kernel<T, Ti, I><<<dim3((unsigned)count), dim3(kBlock), lds, st>>>(
-        items, (const Ti*)strain, (const T*)carriers, (const T*)window, (cpx<T>*)z);
+    allow_lds(node_filter_kernel<T, Ti, I, MAXT>, f.lds);
+    node_filter_kernel<T, Ti, I, MAXT><<<dim3((unsigned)f.count), dim3(kBlock), f.lds, st>>>(
+        f.items, (const Ti*)strain, (const T*)f.carriers, (const T*)f.window, (cpx<T>*)z);
     return hipGetLastError();
 }
 
-hipError_t launch_node_filter(const FilterItem* items, int64_t count, size_t lds, const void* carriers,
-                              const void* window, const void* strain, void* z, int strain_fp64, int fp64,
+template <typename T, typename Ti, int I>
+static hipError_t launch_node_filter_t(const FilterLaunch& f, const void* strain, void* z, hipStream_t st)
+{
+    if (f.tiles == 1) return launch_node_filter_k<T, Ti, I, 1>(f, strain, z, st);
+    if (f.tiles == 2 || filter_tiles(sizeof(T) == 8) == 2) return launch_node_filter_k<T, Ti, I, 2>(f, strain, z, st);
+    if constexpr (filter_tiles(sizeof(T) == 8) == 4) return launch_node_filter_k<T, Ti, I, 4>(f, strain, z, st);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_node_filter(const FilterLaunch& f, const void* strain, void* z, int strain_fp64, int fp64,
                               hipStream_t st)
 {
-    if (count <= 0) return hipSuccess;
-    if (fp64) return launch_node_filter_k<double, double, kImages64>(items, count, lds, carriers, window, strain, z, st);
-    if (strain_fp64)
-        return launch_node_filter_k<float, double, kImages32>(items, count, lds, carriers, window, strain, z, st);
-    return launch_node_filter_k<float, float, kImages32>(items, count, lds, carriers, window, strain, z, st);
+    if (f.count <= 0) return hipSuccess;
+    if (fp64)
+        return f.images == 7 ? launch_node_filter_t<double, double, 7>(f, strain, z, st)
+               : f.images == 9 ? launch_node_filter_t<double, double, 9>(f, strain, z, st)
+                               : hipErrorInvalidValue;
+    if (f.images != 5) return hipErrorInvalidValue;
+    if (strain_fp64) return launch_node_filter_t<float, double, 5>(f, strain, z, st);
+    return launch_node_filter_t<float, float, 5>(f, strain, z, st);
 }
 
 template <typename T, int W, int NE>

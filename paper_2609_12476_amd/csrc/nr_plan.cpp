@@ -109,7 +109,7 @@ struct Chunk {
 struct NodePick {
     double centre;   // centre of its local frequencies, Hz
     double lo, hi;   // least and largest dtau' over its nodes
-    int spacing;     // index into kNodeSpacing
+    int spacing;     // of node_spacing
 };
 
 struct Class {
@@ -138,7 +138,7 @@ struct Class {
     std::vector<int32_t> entry_seg;    // segment of each template-major list entry
     int64_t row_base = 0;              // two-pass sum: first element of the class's power rows
     // node classes: spreading width (0: a sample class), per-instance centre
-    // of the local frequencies and index of the node spacing in kNodeSpacing
+    // of the local frequencies and index of the node spacing
     int node_w = 0;
     int strip = 0;                     // cells of one wave's strip
     std::vector<NodePick> picks;
@@ -240,6 +240,7 @@ struct nr_plan_s {
     DevBuf d_filter[2], d_ftaps[2], d_fwin[2], d_z[2];
     int64_t n_filter[2] = {0, 0};
     size_t filter_lds[2] = {0, 0};
+    int filter_tiles[2] = {0, 0}, filter_images[2] = {0, 0};
     int64_t filter_macs[2] = {0, 0};
     int64_t n_invalid = 0;
     int64_t workspace = 0;
@@ -518,11 +519,12 @@ struct ClassKey {
 // frequency to band-limited values at nodes, and every instance resamples
 // those instead of its samples.
 
-// Samples between nodes, coarsest first (4 times an odd number: the filter's
-// LDS reads are then free of bank conflicts; but for 8 and 16, where twice
-// the nodes would cost more).
-constexpr int kNodeSpacing[] = {172, 148, 124, 100, 84, 76, 68, 60, 52, 44, 36, 28, 20, 16, 12, 8, 4};
-constexpr int kNodeSpacings = sizeof(kNodeSpacing) / sizeof(kNodeSpacing[0]);
+// Samples between nodes, coarsest first: 174, 170 .. 2 in FP32, 85, 83 .. 1 in
+// FP64.  The filter's LDS reads of 16 nodes are free of bank conflicts for 2
+// (mod 4) in FP32 and odd spacings in FP64, and a workgroup's window of samples
+// stays below 64 KB (FP32) or 80 KB.
+constexpr int kNodeSpacings = 43;
+int node_spacing(int fp64, int s) { return fp64 ? 85 - 2 * s : 174 - 4 * s; }
 
 // Of the node rate R, the share between the edges of the pass band and of its
 // first image: the narrower, the fewer nodes and the longer the filter.
@@ -547,14 +549,20 @@ int node_width(int fp64, int w)
 
 // Attenuation of the filter in dB and its half-width in nodes (Kaiser's
 // estimate of the length of a window for that attenuation and transition).
-// FP32: 150 dB, 3e-8, half the rounding of one FP32 value.
-double node_attenuation(int fp64, int node_w) { return !fp64 ? 150.0 : node_w == 12 ? 230.0 : 270.0; }
+// FP32: 150 dB, 3e-8, half the rounding of one FP32 value.  FP64 of width 12:
+// 218 dB, 1.2e-11 under a kernel error of 3.3e-11.
+double node_attenuation(int fp64, int node_w) { return !fp64 ? 150.0 : node_w == 12 ? 218.0 : 270.0; }
+// Images of the filter's window on one period of the carriers (odd).
+int node_images(int fp64, int node_w) { return !fp64 ? 5 : node_w == 12 ? 7 : 9; }
 int node_half(int fp64, int node_w)
 {
     const int half =
         (int)std::ceil((node_attenuation(fp64, node_w) - 7.95) / (2.285 * 2.0 * M_PI * kNodeTransition) / 2.0);
-    return std::min(half, (fp64 ? kImages64 : kImages32) * kNodeRefs / 2);   // the window's images cover it
+    return std::min(half, node_images(fp64, node_w) * kNodeRefs / 2);   // the window's images cover it
 }
+// Steps of four cells of a small grid's DFT, a multiple of four.
+int node_dft_half(int n) { return (n + 15) / 16 * 4; }
+
 // Coefficients per parity of the node spreader's kernel pieces.
 int node_coefs(int node_w) { return node_w == 8 ? 4 : node_w == 12 ? 7 : 9; }
 int node_count(int64_t L, int D, int half) { return (int)((L - 1) / D) + 2 * half; }
@@ -570,11 +578,10 @@ bool pick_nodes(const InstHost& h, const nr_segment& g, const nr_template& t, do
     const double f0 = t.f_lo, f1 = t.f_lo + (t.n_bins - 1) * df;
     const double c = h.beta == 0.0 ? 0.0 : (double)h.c;
     const double r0 = h.beta == 0.0 ? 1.0 : std::pow(h.us, -0.375);
-    const double most = fp64 ? 84 : 172;          // the filter's window of samples stays in LDS
     for (int s = 0; s < kNodeSpacings; ++s) {
-        const int D = kNodeSpacing[s];
+        const int D = node_spacing(fp64, s);
         // rates that do not even hold the band at rest need no closer look
-        if (D > most || g.fs < 0.5 * kNodeMinRate * (f1 - f0) * r0 * D) continue;
+        if (g.fs < 0.5 * kNodeMinRate * (f1 - f0) * r0 * D) continue;
         const double before = (double)(half - 1) * D, after = (double)(g.n_samples - 1) + (double)half * D;
         if (c * after >= 0.9 || c * before >= 0.9) continue;
         const double lo = r0 * std::pow(1.0 + c * before, -0.375), hi = r0 * std::pow(1.0 - c * after, -0.375);
@@ -762,7 +769,7 @@ void build_class_tables(Class& c, double tol_cls, double sigma)
         // rows of the small DFT (see node_spread_dft_kernel): lane l of a step
         // holds A[row l % 16][column l / 16], the columns being the grid's
         // real, then its imaginary parts
-        const int half = (c.n + 3) / 4, tiles = (2 * c.kmax + 15) / 16, m0 = c.kmax / 2;
+        const int half = node_dft_half(c.n), tiles = (2 * c.kmax + 15) / 16, m0 = c.kmax / 2;
         std::vector<long double> dft((size_t)tiles * 2 * half * 64, 0.0L);
         for (int tile = 0; tile < tiles; ++tile)
             for (int g = 0; g < 4; ++g)
@@ -797,7 +804,7 @@ void build_groups(nr_plan_s& P);
 // of a matrix step fall on distinct banks.
 int node_stride(const Class& c)
 {
-    return (std::max(2 * c.strip, 8 * ((c.n + 3) / 4)) + 3) / 8 * 8 + 4;
+    return (std::max(2 * c.strip, 8 * node_dft_half(c.n)) + 3) / 8 * 8 + 4;
 }
 size_t node_lds_bytes(const Class& c)
 {
@@ -853,7 +860,7 @@ bool plan_nodes(nr_plan_s& P)
     // lane-operations of one node round of an instance, and of the filter of
     // one segment for `tiles` tiles
     auto nodes_of = [](const Shape& sh, int s) {
-        return node_count(sh.L, kNodeSpacing[s], node_half(sh.fp64, sh.node_w));
+        return node_count(sh.L, node_spacing(sh.fp64, s), node_half(sh.fp64, sh.node_w));
     };
     auto spread_cost = [&](const Shape& sh, int s) {
         return (double)((nodes_of(sh, s) + kWave - 1) / kWave) * kWave * (sh.fp64 ? 170.0 : 85.0);
@@ -862,8 +869,8 @@ bool plan_nodes(nr_plan_s& P)
     // rate in FP32, and the folding
     auto filter_cost = [&](const Shape& sh, int s, int tiles) {
         const double chunks = (double)((nodes_of(sh, s) + kNodeTile - 1) / kNodeTile);
-        return chunks * kNodeTile * (0.5 * kNodeRefs * kNodeSpacing[s] + 8.0) *
-               (2.0 * tiles * kFilterRows * (sh.fp64 ? 1.0 : 0.5) + 5.0 * (sh.fp64 ? kImages64 : kImages32));
+        return chunks * kNodeTile * (0.5 * kNodeRefs * node_spacing(sh.fp64, s) + 8.0) *
+               (2.0 * tiles * kFilterRows * (sh.fp64 ? 1.0 : 0.5) + 5.0 * node_images(sh.fp64, sh.node_w));
     };
     for (auto& kv : shapes) {
         const Shape& sh = kv.first;
@@ -876,7 +883,7 @@ bool plan_nodes(nr_plan_s& P)
             int next = s + 1;
             while (next < kNodeSpacings && kv.second[next].count == 0) ++next;
             if (next == kNodeSpacings) continue;
-            const double refs = (u.f_hi - u.f_lo) * kNodeRefs * kNodeSpacing[s] / sh.fs + 1.0;
+            const double refs = (u.f_hi - u.f_lo) * kNodeRefs * node_spacing(sh.fp64, s) / sh.fs + 1.0;
             const double own = filter_cost(sh, s, (int)std::min(1e6, std::ceil(refs / kFilterRows))) *
                                (double)std::min<int64_t>(u.count, P.n_segs);
             if ((double)u.count * (spread_cost(sh, next) - spread_cost(sh, s)) < own) {
@@ -887,13 +894,21 @@ bool plan_nodes(nr_plan_s& P)
                 u.final_s = next;
             }
         }
+        // and what is left moves on to the finest spacing of as many rounds: a
+        // shorter period of the carriers and fewer of them at the same nodes
         for (int s = kNodeSpacings - 1; s >= 0; --s) {
             Use& u = kv.second[s];
-            if (u.final_s >= 0 && u.final_s != s) u.final_s = kv.second[u.final_s].final_s;
+            if (u.count == 0) continue;
+            if (u.final_s != s) {
+                u.final_s = kv.second[u.final_s].final_s;
+                continue;
+            }
+            while (u.final_s + 1 < kNodeSpacings && spread_cost(sh, u.final_s + 1) == spread_cost(sh, s)) ++u.final_s;
         }
+        P.filter_images[sh.fp64] = std::max(P.filter_images[sh.fp64], node_images(sh.fp64, sh.node_w));
     }
     auto ref_of = [](const NodePick& p, const Shape& sh) {
-        return (int)std::lround(p.centre * (kNodeRefs * kNodeSpacing[p.spacing]) / sh.fs);
+        return (int)std::lround(p.centre * (kNodeRefs * node_spacing(sh.fp64, p.spacing)) / sh.fs);
     };
     each([&](Class&, InstDev&, NodePick& p, const Shape& sh, std::array<Use, kNodeSpacings>& u) {
         p.spacing = u[p.spacing].final_s;
@@ -940,8 +955,8 @@ bool plan_nodes(nr_plan_s& P)
             const Shape& sh = kv.first;
             Use& u = kv.second[s];
             if (u.lo > u.hi) continue;
-            const int f = sh.fp64, D = kNodeSpacing[s], half = node_half(f, sh.node_w), NB = node_count(sh.L, D, half);
-            const int Q = kNodeRefs * D, images = f ? kImages64 : kImages32, stride = (images + 3) / 4 * 4;
+            const int f = sh.fp64, D = node_spacing(f, s), half = node_half(f, sh.node_w), NB = node_count(sh.L, D, half);
+            const int Q = kNodeRefs * D, images = P.filter_images[f], stride = (images + 3) / 4 * 4;
             const int ksteps = (Q / 2 + 1 + 15) / 16;
             FilterItem it{};
             it.D = D;
@@ -980,7 +995,7 @@ bool plan_nodes(nr_plan_s& P)
                 for (int t = 0; t < u.tiles;) {
                     int64_t* at = &u.z_off[(size_t)g * u.tiles + t];
                     int run = 0;
-                    while (run < kFilterTiles && t + run < u.tiles && at[run] >= 0) {
+                    while (run < filter_tiles(f) && t + run < u.tiles && at[run] >= 0) {
                         at[run] = z[f] + (int64_t)run * kFilterRows * NB;
                         ++run;
                     }
@@ -992,6 +1007,7 @@ bool plan_nodes(nr_plan_s& P)
                         for (it.node0 = 0; it.node0 < NB; it.node0 += kNodeTile) items[f].push_back(it);
                         z[f] += (int64_t)run * kFilterRows * NB;
                         node_cost += filter_cost(sh, s, run);
+                        P.filter_tiles[f] = std::max(P.filter_tiles[f], run);
                         P.filter_macs[f] += (int64_t)((NB + kNodeTile - 1) / kNodeTile) * kNodeTile * 16 * ksteps *
                                             (2 * run * kFilterRows + 2 * images);
                     }
@@ -1003,7 +1019,7 @@ bool plan_nodes(nr_plan_s& P)
     each([&](Class& c, InstDev& d, NodePick& p, const Shape& sh, std::array<Use, kNodeSpacings>& u) {
         const Use& v = u[p.spacing];
         const int half = node_half(sh.fp64, sh.node_w), rank = v.rank[ref_of(p, sh) - v.lo];
-        d.C = kNodeSpacing[p.spacing];
+        d.C = node_spacing(sh.fp64, p.spacing);
         d.nodes = node_count(sh.L, d.C, half);
         // cells from one node to the next, at least and at most; a lane's nodes
         // (consecutive ones) put a cell between it and the next lane
@@ -1030,7 +1046,7 @@ bool plan_nodes(nr_plan_s& P)
         P.d_filter[f].upload(items[f], "filter work");
         upload_as(P.d_ftaps[f], f, carriers[f], "filter carriers");
         upload_as(P.d_fwin[f], f, window[f], "filter window");
-        P.d_z[f].alloc((size_t)z[f] * (f ? 16 : 8), "node values");
+        P.d_z[f].alloc((size_t)(z[f] + 1) * (f ? 16 : 8), "node values");   // one spare: nodes are read in pairs
     }
     return true;
 }
@@ -1664,8 +1680,8 @@ NodeArgs node_args(const nr_plan_s& P, const Class& c)
     a.strip = c.strip;
     if (c.n <= kNodeDftMax) {
         a.mtiles = (2 * c.kmax + 15) / 16;
-        a.ksteps = 2 * ((c.n + 3) / 4);
-        a.im_off = 4 * ((c.n + 3) / 4);
+        a.ksteps = 2 * node_dft_half(c.n);
+        a.im_off = 4 * node_dft_half(c.n);
         a.gstride = node_stride(c);
     }
     return a;
@@ -1814,8 +1830,9 @@ void lane_major(nr_plan_s& P, const void* strain)
     for (int f = 0; f < 2; ++f)
         if (P.n_filter[f])
             timed_launch(P, NR_STAGE_LAYOUT, [&] {
-                return launch_node_filter((const FilterItem*)P.d_filter[f].p, P.n_filter[f], P.filter_lds[f],
-                                          P.d_ftaps[f].p, P.d_fwin[f].p, strain, P.d_z[f].p, P.strain_fp64, f, P.stream);
+                const FilterLaunch fl{(const FilterItem*)P.d_filter[f].p, P.n_filter[f], P.filter_tiles[f], P.filter_images[f],
+                                      P.filter_lds[f], P.d_ftaps[f].p, P.d_fwin[f].p};
+                return launch_node_filter(fl, strain, P.d_z[f].p, P.strain_fp64, f, P.stream);
             }, "node filter");
 }
 
@@ -2452,7 +2469,7 @@ nr_status nufft_resample_query_nodes(nr_plan p, int32_t ci, nr_node_info* info)
     info->width = c.node_w;
     info->degree = 2 * node_coefs(c.node_w) - 1;
     for (const InstDev& d : c.inst) info->nodes += d.nodes;
-    info->values = (int64_t)p->d_z[c.fp64].bytes / (c.fp64 ? 16 : 8);
+    info->values = (int64_t)p->d_z[c.fp64].bytes / (c.fp64 ? 16 : 8) - 1;
     info->filter_macs = p->filter_macs[c.fp64];
     return NR_OK;
 }
