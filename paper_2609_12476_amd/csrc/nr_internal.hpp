@@ -82,7 +82,7 @@ struct SpreadArgs {
     int64_t pt_base;         // pt_off of the first instance of the chunk
     int32_t n;               // grid size
     int32_t w;               // kernel width
-    int32_t parts;           // waves per instance (1, 2, 4, 8 or 16)
+    int32_t parts;           // waves per instance (1, 2, 4, 8 or 16; with records a multiple of 4)
     int32_t flush_period;    // steps between collective flushes (power of two)
     int32_t strain_complex;
     int32_t snap;            // 1: cumulative moments with snapshots; 0: per-cell moments
@@ -98,6 +98,10 @@ struct SpreadArgs {
     // single-class launches: logical workgroup of each hardware workgroup
     // (NULL: the identity)
     const int32_t* block_order;
+    // cell runs with records: cells of one record (64 + w - 1; 0: grids), and
+    // the shares of a round's runs, 2^rec_shift
+    int32_t rec_stride;
+    int32_t rec_shift;
 };
 
 // Workgroups of one launch of a class chunk, and grid slots per instance:
@@ -108,6 +112,10 @@ __host__ __device__ inline int64_t spread_blocks(int64_t count, int parts)
 {
     return parts > 4 ? count * (parts / 4) : (count * parts + 3) / 4;
 }
+
+// Cells of an instance's records: a header (first cell, rounds) and one record
+// per wave.
+__host__ __device__ inline int64_t rec_cells(int parts, int rec_stride) { return 1 + (int64_t)parts * rec_stride; }
 
 struct EpilogueArgs {
     const InstDev* inst;
@@ -129,6 +137,10 @@ struct EpilogueArgs {
     // two-pass segment sum: power rows of the class, one per list entry
     int64_t row_base;              // first element of the class's rows (row e at row_base + e kmax)
     const int32_t* entry_seg;      // segment of each list entry
+    // records of cell runs instead of partial grids (as in SpreadArgs)
+    int32_t parts;
+    int32_t rec_stride;
+    int32_t rec_shift;
 };
 
 // Per-call pointers of the epilogue (the same for every class of a plan).

@@ -392,6 +392,13 @@ struct Moments {
     }
 };
 
+// Coefficients of how many taps are loaded ahead of their use (scalar
+// registers; the scalar loads of one tap after the other are a serial chain:
+// 30720 samples on 1200 cells in FP64 by eight waves took 68 us, 64 so and with
+// the strain of the next step on its way).
+template <typename T, int D>
+constexpr int kTapsAhead = (D + 1) * sizeof(T) <= 32 ? 4 : 2;
+
 // Turn the moments of every point whose support starts at cell g into the
 // w tap sums and add them to the wave's LDS grid:
 //   tap t = sum_p A[t][p] M_p, added at cell (g + t) mod n.
@@ -402,6 +409,7 @@ __device__ __forceinline__ void flush(const Moments<T, D>& M, int g, const T* __
     // g may be any integer (an unwrapped cell index): reduce it mod n once
     g %= n;
     if (g < 0) g += n;
+#pragma unroll kTapsAhead<T, D>
     for (int t = 0; t < w; ++t) {
         const T* At = A + t * (D + 1);
         T vr = T(0), vi = T(0);
@@ -447,16 +455,17 @@ __device__ __forceinline__ double wave_shift(double v)
 // v with the sum of tap_s of lane v - s over s, everything that this round
 // adds to its cell g; the same chain with rotation, fed only by the lanes
 // whose supports pass the round's last cell (v >= 65 - w), leaves lanes
-// v < w - 1 with what lands on cell g + 64.  Each lane then makes one LDS
-// addition per component (two for the lanes carrying that spill) instead of
-// w.  Every lane takes part (empty runs have zero moments), and the order of
-// the additions is fixed, so the result does not depend on scheduling.
+// v < w - 1 with what lands on cell g + 64.  Each lane then makes one addition
+// per component (two for the lanes carrying that spill) instead of w.  Every
+// lane takes part (empty runs have zero moments), and the order of the
+// additions is fixed, so the result does not depend on scheduling.
 template <typename T, int D>
-__device__ __forceinline__ void flush_round(const Moments<T, D>& M, int g, int lane, const T* __restrict__ A,
-                                            cpx<T>* grid, int n, int w)
+__device__ __forceinline__ void round_sums(const Moments<T, D>& M, int lane, const T* __restrict__ A, int w,
+                                           cpx<T>& own, cpx<T>& past)
 {
     const bool spill = lane >= kWave + 1 - w;
     T hr = T(0), hi = T(0), sr = T(0), si = T(0);
+#pragma unroll kTapsAhead<T, D>
     for (int t = w - 1; t >= 0; --t) {
         const T* At = A + t * (D + 1);
         T vr = T(0), vi = T(0);
@@ -470,14 +479,24 @@ __device__ __forceinline__ void flush_round(const Moments<T, D>& M, int g, int l
         sr = wave_shift<true>(sr) + (spill ? vr : T(0));
         si = wave_shift<true>(si) + (spill ? vi : T(0));
     }
+    own = cpx<T>{hr, hi};
+    past = cpx<T>{sr, si};
+}
+
+template <typename T, int D>
+__device__ __forceinline__ void flush_round(const Moments<T, D>& M, int g, int lane, const T* __restrict__ A,
+                                            cpx<T>* grid, int n, int w)
+{
+    cpx<T> h, s;
+    round_sums<T, D>(M, lane, A, w, h, s);
     int c = g % n;
     if (c < 0) c += n;
-    lds_add(&grid[c].x, hr);
-    lds_add(&grid[c].y, hi);
+    lds_add(&grid[c].x, h.x);
+    lds_add(&grid[c].y, h.y);
     if (lane < w - 1) {
         const int c2 = (c + kWave) % n;
-        lds_add(&grid[c2].x, sr);
-        lds_add(&grid[c2].y, si);
+        lds_add(&grid[c2].x, s.x);
+        lds_add(&grid[c2].y, s.y);
     }
 }
 
@@ -635,7 +654,6 @@ __device__ __forceinline__ void spread_block(const SpreadArgs& a, const Epilogue
         const P* __restrict__ pts =
             FUSED ? nullptr
                   : reinterpret_cast<const P*>(a.points) + (d.pt_off - a.pt_base) + row0;
-        const int64_t xs0 = d.strain_off + row0;
         const int fmask = a.flush_period - 1;
         // fused: grid position in cells and phase in table steps per unit dtau
         const double dfn = tc.df * (double)n, hnn = tc.hn * (double)n;
@@ -651,16 +669,22 @@ __device__ __forceinline__ void spread_block(const SpreadArgs& a, const Epilogue
         // cells are unwrapped integers on the fused path (any sign)
         constexpr int kNone = INT_MIN;
         int g_cur = kNone, g_pend = kNone;
+        // the strain of the next step is on its way during this one (the copy
+        // is padded to C steps)
+        using X = typename std::conditional<CPLX, cpx<T>, T>::type;
+        const X* __restrict__ xs = reinterpret_cast<const X*>(a.strain_lm) + d.strain_off + row0;
+        X xnext = xs[0];
         for (int s = 0; s < C; ++s) {
             const int j = v * C + s;
+            const X x = xnext;
+            xnext = xs[(int64_t)(s + 1 < C ? s + 1 : s) * kWave];
             if (j < L) {
                 T xr, xi;
-                if (CPLX) {
-                    const cpx<T> xv = reinterpret_cast<const cpx<T>*>(a.strain_lm)[xs0 + (int64_t)s * kWave];
-                    xr = xv.x;
-                    xi = xv.y;
+                if constexpr (CPLX) {
+                    xr = x.x;
+                    xi = x.y;
                 } else {
-                    xr = reinterpret_cast<const T*>(a.strain_lm)[xs0 + (int64_t)s * kWave];
+                    xr = x;
                     xi = T(0);
                 }
                 const Decoded<T> q = FUSED ? decode_dt<T, CPLX>(dtau_of<false>(tc, j), dfn, hnn, fcs, xr, xi, tab)
@@ -727,8 +751,19 @@ __global__ __launch_bounds__(kBlock) void spread_kernel(SpreadArgs a, EpilogueOu
 // lane 62's run), every lane accumulates its run's moments without a cell
 // change (its Chebyshev
 // variable is 1 - 2 (S_j - U), from the same S_j that placed the sample in
-// the run), and all lanes flush together.  The strain is read as aligned
-// quads of samples from a plain per-segment copy.
+// the run), and all lanes flush together.  The strain is read in quads of
+// samples from a plain per-segment copy.
+//
+// Where the rounds end: in the wave's grid copy in LDS, or (classes with
+// records, SpreadArgs::rec_stride > 0) each round's 64 + w - 1 cells in a
+// record of its own in global memory, from which the epilogue gathers the
+// grid.  A plan too small to fill the GPU is a matter of latency: with a grid
+// copy per wave a wave zeroes and sums n cells for the few rounds that it
+// does, and 16 n cells of FP64 leave one workgroup a compute unit.  With
+// records a wave does one round (or one of 2^rec_shift shares of its runs),
+// needs no grid, and classes of every grid size share a launch.  One FP64
+// instance of 15360 samples on 2400 cells: 47 -> 30 us a call, 512 of them 219
+// -> 109; bound by the latency of the search, the run and the flush.
 
 __device__ __forceinline__ double grid_coord(double dfn, double hnn, double dt) { return fma(dfn, dt, -hnn); }
 
@@ -782,8 +817,9 @@ __device__ __forceinline__ int first_at_least(const TauConsts& tc, int L, double
     }
 }
 
+// (aligned as its elements: a run starts at any sample)
 template <typename E>
-struct alignas(16) Quad {
+struct Quad {
     E v[4];
 };
 
@@ -802,7 +838,8 @@ __device__ __forceinline__ void cell_quad(const TauConsts& tc, double top, const
     for (int e = 0; e < 4; ++e) {
         const int j = q + e;
         const bool in = MASK ? ((j >= js) & (j < je)) : true;
-        const T u = (T)fma(-2.0, grid_coord(dfn, hnn, dt[e]), u1);
+        const T v = (T)fma(-2.0, grid_coord(dfn, hnn, dt[e]), u1);
+        const T u = in ? v : T(0);   // (powers of a far sample's position could overflow)
         T xr, xi, cr, ci;
         if constexpr (CPLX) {
             xr = in ? xq.v[e].x : T(0);
@@ -833,7 +870,9 @@ __device__ __forceinline__ void spread_runs_block(const SpreadArgs& a, const Epi
     cpx<T>* grid = lds + wave * grid_stride(a, wpi);
     const cpx<T>* gtab = reinterpret_cast<const cpx<T>*>(a.phase_table);
     for (int k = threadIdx.x; k < NT; k += kBlock) tab[k] = gtab[k];
-    for (int c = lane; c < n; c += kWave) grid[c] = cpx<T>{T(0), T(0)};
+    const bool rec = a.rec_stride > 0;
+    if (!rec)
+        for (int c = lane; c < n; c += kWave) grid[c] = cpx<T>{T(0), T(0)};
     __syncthreads();
 
     int64_t item;
@@ -859,43 +898,69 @@ __device__ __forceinline__ void spread_runs_block(const SpreadArgs& a, const Epi
         const double fcs = tc.fc * (double)(1 << kPhaseShift<T>);
         const double S1 = grid_coord(dfn, hnn, dtau_of<false>(tc, L > 0 ? L - 1 : 0));
         const double U0 = floor(-hnn), U1 = floor(S1);
-        const int rounds = L > 0 ? uniform(((int)(U1 - U0) + kRunsPerRound) / kRunsPerRound) : 0;
+        int rounds = L > 0 ? uniform(((int)(U1 - U0) + kRunsPerRound) / kRunsPerRound) : 0;
+        if (rec && rounds > (parts >> a.rec_shift)) rounds = parts >> a.rec_shift;   // (the plan counts no fewer)
         // reciprocal slopes of the chord and of the tangent at j = 0
         const double inv_m = L > 1 ? (double)(L - 1) / (S1 + hnn) : 0.0;
         const double inv_s0 = 1.0 / (dfn * (tc.ndeg > 0 ? tc.bc[0] : tc.c));
         const E* __restrict__ xs = reinterpret_cast<const E*>(a.strain_lm) + d.strain_off;
+        const int last_quad = ((L + kWave - 1) & ~(kWave - 1)) - 4;   // of the segment's copy
         // leading series coefficient, kept in a vector register
         double top = tc.ndeg > 0 ? tc.b[tc.ndeg - 1] : 0.0;
         asm volatile("" : "+v"(top));
-        for (int r = part; r < rounds; r += parts) {
+        // with records: wave 'part' of the instance takes sub-run part mod
+        // 2^rec_shift of every run of one round and stores the round's sums
+        const int sub = part & ((1 << a.rec_shift) - 1);
+        cpx<T>* area = reinterpret_cast<cpx<T>*>(a.grid) + item * rec_cells(parts, a.rec_stride);
+        if (rec && part == 0 && lane == 0) {
+            int c0 = ((int)U0 + 1) % n;
+            if (c0 < 0) c0 += n;
+            *reinterpret_cast<int2*>(area) = make_int2(c0, rounds);
+        }
+        for (int r = rec ? part >> a.rec_shift : part; r < rounds; r += parts) {
             // lane v < 63: cell U = U0 + 63 r + v; every lane searches the
             // start of its cell's run (the first sample at or past cell U),
             // lanes v < 63 take the end from lane v + 1, and lane 63 takes
             // no cell (its search gives lane 62's end), so one search per
             // lane and round serves both ends
             const double U = U0 + (double)(kRunsPerRound * r + lane);
-            const int js = (r == 0 && lane == 0) ? 0       // S_0 >= U0 = floor(S_0)
-                                                 : first_at_least(tc, L, U, dfn, hnn, inv_m, inv_s0);
+            int js = (r == 0 && lane == 0) ? 0             // S_0 >= U0 = floor(S_0)
+                                           : first_at_least(tc, L, U, dfn, hnn, inv_m, inv_s0);
             int je = dpp_shl1(js);
             if (lane == kWave - 1) je = js;
+            if (a.rec_shift) {
+                const int len = je - js;
+                je = js + (int)(((int64_t)len * (sub + 1)) >> a.rec_shift);
+                js += (int)(((int64_t)len * sub) >> a.rec_shift);
+            }
             const double u1 = fma(2.0, U, 1.0);
             Moments<T, D> M;
             M.zero();
-            // whole quads: the first and last quad of a run are masked
-            // (samples outside it enter with zero strength; they lie in the
-            // padded copy and have finite positions), the ones between are not
-            if (je > js) {
-                int q = js & ~3;
-                double jq = (double)q;
-                cell_quad<T, D, CPLX, true>(tc, top, xs, q, jq, js, je, dfn, hnn, u1, fcs, tab, M);
-                for (q += 4, jq += 4.0; q + 4 <= je; q += 4, jq += 4.0)
-                    cell_quad<T, D, CPLX, false>(tc, top, xs, q, jq, js, je, dfn, hnn, u1, fcs, tab, M);
-                if (q < je) cell_quad<T, D, CPLX, true>(tc, top, xs, q, jq, js, je, dfn, hnn, u1, fcs, tab, M);
+            // quads from the run's first sample on, wherever it lies (16-byte
+            // loads need no more than the element's alignment); the last one is
+            // masked (samples outside the run enter with zero strength) and
+            // moved back where it would pass the copy's padding
+            int q = js;
+            double jq = (double)js;
+            for (; q + 4 <= je; q += 4, jq += 4.0)
+                cell_quad<T, D, CPLX, false>(tc, top, xs, q, jq, q, je, dfn, hnn, u1, fcs, tab, M);
+            if (q < je) {
+                const int qm = q < last_quad ? q : last_quad;
+                cell_quad<T, D, CPLX, true>(tc, top, xs, qm, (double)qm, q, je, dfn, hnn, u1, fcs, tab, M);
             }
             // the support of the points of cell U starts at cell U + 1
-            flush_round<T, D>(M, (int)U + 1, lane, A, grid, n, w);
+            if (rec) {
+                cpx<T> h, s;
+                round_sums<T, D>(M, lane, A, w, h, s);
+                cpx<T>* to = area + 1 + (int64_t)part * a.rec_stride;
+                to[lane] = h;
+                if (lane < w - 1) to[kWave + lane] = s;
+            } else {
+                flush_round<T, D>(M, (int)U + 1, lane, A, grid, n, w);
+            }
         }
     }
+    if (rec) return;
     __syncthreads();
     finish_instance<T>(a, o, item, slot, lds, wave, lane, wpi);
 }
@@ -949,12 +1014,45 @@ __device__ __forceinline__ cpx<T>* stage_twiddles(unsigned char* smem, const voi
     return tw;
 }
 
-// Load an instance's grid (sum of its partial grids, in slot order) into
-// the team's buffer.
+// Load an instance's grid into the team's buffer: the sum of its partial
+// grids in slot order, or of the records of its rounds.  Cell c is cell
+// e = c - c0 (mod n) after the first one that the instance reaches, and every
+// n-th after that: position e - 63 r of round r's record and, for the first
+// w - 1 cells of a round, 63 further on in the round before.
 template <typename T>
 __device__ __forceinline__ void load_grid(const EpilogueArgs& a, int64_t local, cpx<T>* buf, int tid, int ts)
 {
     const int n = a.fft.n;
+    if (a.rec_stride > 0) {
+        const cpx<T>* area = reinterpret_cast<const cpx<T>*>(a.grid) + local * rec_cells(a.parts, a.rec_stride);
+        const int2 hdr = *reinterpret_cast<const int2*>(area);
+        const int rounds = hdr.y, spill = a.rec_stride - kWave, shares = 1 << a.rec_shift;
+        const int end = kRunsPerRound * rounds + spill;
+        const cpx<T>* rec = area + 1;
+        for (int c = tid; c < n; c += ts) {
+            int e = c - hdr.x;
+            if (e < 0) e += n;
+            cpx<T> v{T(0), T(0)};
+            for (; e < end; e += n) {
+                const int r = (int)((uint32_t)e / (uint32_t)kRunsPerRound), o = e - r * kRunsPerRound;
+                for (int q = 0; q < shares; ++q) {
+                    const cpx<T>* at = rec + (int64_t)((r << a.rec_shift) + q) * a.rec_stride;
+                    if (r > 0 && o < spill) {
+                        const cpx<T> u = at[o + kRunsPerRound - (int64_t)shares * a.rec_stride];
+                        v.x += u.x;
+                        v.y += u.y;
+                    }
+                    if (r < rounds) {
+                        const cpx<T> u = at[o];
+                        v.x += u.x;
+                        v.y += u.y;
+                    }
+                }
+            }
+            buf[c] = v;
+        }
+        return;
+    }
     const cpx<T>* g = reinterpret_cast<const cpx<T>*>(a.grid) + local * a.slots * n;
     for (int c = tid; c < n; c += ts) {
         cpx<T> v = g[c];
@@ -1265,6 +1363,10 @@ __global__ __launch_bounds__(kBlock) void direct_kernel(SpreadArgs a, EpilogueAr
 
 // Lane-major copies: blockIdx.x picks the class segment, blockIdx.y and the
 // thread stride over its entries in order, so the stores are contiguous.
+// Plain copies (C = 1) take kCopyAhead entries a thread, all loads first: with
+// one entry at a time, 16 of them one after the other, one segment of 7680
+// samples took 5.1 us, now 2.6.
+constexpr int kCopyAhead = 4;
 template <typename Ti, typename To>
 __global__ __launch_bounds__(kBlock) void strain_lane_major_kernel(const SegDev* __restrict__ segs,
                                                                    const Ti* __restrict__ src, int cplx)
@@ -1273,6 +1375,22 @@ __global__ __launch_bounds__(kBlock) void strain_lane_major_kernel(const SegDev*
     To* __restrict__ dst = reinterpret_cast<To*>(sd.dst);
     const uint32_t run = (uint32_t)sd.C * kWave;  // entries of 64 lane runs
     const uint32_t total = (uint32_t)sd.parts * run;
+    if (sd.C == 1) {
+        const int per = cplx ? 2 : 1;
+        const Ti* __restrict__ from = src + per * sd.src_off;
+        To* __restrict__ to = dst + per * sd.dst_off;
+        const int64_t have = (int64_t)per * sd.L, all = (int64_t)per * total;
+        for (int64_t o = (int64_t)blockIdx.y * (kBlock * kCopyAhead) + threadIdx.x; o < all;
+             o += (int64_t)kBlock * kCopyAhead * gridDim.y) {
+            Ti v[kCopyAhead];
+#pragma unroll
+            for (int k = 0; k < kCopyAhead; ++k) v[k] = o + k * kBlock < have ? from[o + k * kBlock] : Ti(0);
+#pragma unroll
+            for (int k = 0; k < kCopyAhead; ++k)
+                if (o + k * kBlock < all) to[o + k * kBlock] = (To)v[k];
+        }
+        return;
+    }
     for (uint32_t o = blockIdx.y * kBlock + threadIdx.x; o < total; o += kBlock * gridDim.y) {
         const uint32_t blk = o / run, rem = o - blk * run;
         const uint32_t srow = rem / kWave, lane = rem - srow * kWave;
@@ -1351,8 +1469,8 @@ hipError_t launch_strain_lane_major(const SegDev* segs, int32_t n_segs, int64_t 
                                     int strain_fp64, int strain_complex, int dst_fp64, hipStream_t st)
 {
     if (n_segs <= 0) return hipSuccess;
-    // about 16 entries per thread of the largest segment, at most 64 workgroups per segment
-    int64_t gy = (max_entries + kBlock * 16 - 1) / (kBlock * 16);
+    // kCopyAhead entries per thread of the largest segment, at most 64 workgroups per segment
+    int64_t gy = (max_entries + kBlock * kCopyAhead - 1) / (kBlock * kCopyAhead);
     if (gy < 1) gy = 1;
     if (gy > 64) gy = 64;
     dim3 grid((unsigned)n_segs, (unsigned)gy), block(kBlock);
@@ -1474,7 +1592,7 @@ hipError_t launch_spread(const SpreadArgs& a, int fp64, int deg, int fused, cons
 {
     if (a.count <= 0) return hipSuccess;
     const int64_t blocks = spread_blocks(a.count, a.parts);
-    const size_t lds = spread_lds_bytes(fp64, a.n, a.epi_fused && a.parts == 1);
+    const size_t lds = spread_lds_bytes(fp64, a.rec_stride ? 0 : a.n, a.epi_fused && a.parts == 1);
     return fp64 ? launch_spread_t<double>(a, out, deg, fused, a.strain_complex, a.snap, blocks, lds, st)
                 : launch_spread_t<float>(a, out, deg, fused, a.strain_complex, a.snap, blocks, lds, st);
 }

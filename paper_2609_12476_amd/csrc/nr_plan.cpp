@@ -141,10 +141,26 @@ struct Class {
     // of the local frequencies and index of the node spacing
     int node_w = 0;
     int strip = 0;                     // cells of one wave's strip
+    // cell runs with records (cells of one, 0: partial grids) and the shares of
+    // a round's runs, 2^rec_shift; rounds of the instance with the most
+    int rec_stride = 0, rec_shift = 0, rounds = 0;
+    double run_samples = 0.0;          // samples per cell, likewise the most
     std::vector<NodePick> picks;
     DevBuf d_inst, d_coef, d_taps, d_dec, d_tw, d_phase, d_strain, d_tmpl_id, d_tmpl_list,
         d_tmpl_list_off, d_tmpl_stat_off, d_entry_seg, d_order, d_dft;
 };
+
+// Bytes that one instance of a class needs in the grid buffer: its partial
+// grids or records (the direct baseline and the node classes need neither).
+int64_t grid_bytes(const Class& c)
+{
+    if (c.method == NR_METHOD_DIRECT || c.node_w) return 0;
+    const int64_t cells = c.rec_stride ? rec_cells(c.parts, c.rec_stride) : (int64_t)c.n * grid_slots(c.parts);
+    return cells * (c.fp64 ? 16 : 8);
+}
+
+// LDS of a class's spreader workgroup.
+size_t class_lds(const Class& c) { return spread_lds_bytes(c.fp64, c.rec_stride ? 0 : c.n, c.fuse_epi && c.parts == 1); }
 
 // XCD-aware workgroup order.  The GPU deals the workgroups of a launch to its
 // eight XCDs in turn (workgroup b to XCD b mod 8), and each XCD has its own
@@ -154,6 +170,7 @@ struct Class {
 // meets mostly its own segments (measured on the 1 h workload: strain fetched
 // about 2.8 times instead of 8, since a full GPU does not keep strict turns).
 constexpr int kXcds = 8;
+constexpr int kCus = 256;
 constexpr int64_t kOrderMinBlocks = 2048;
 
 void build_block_order(Class& c)
@@ -197,6 +214,7 @@ struct Group {
     int fp64 = 0, deg = 0, fused = 1, snap = 0;
     int fuse_epi = 0;                  // epilogue groups: classes whose spreader writes the outputs
     size_t lds[2] = {0, 0};            // spread: [0]; epilogue: [0] spectra, [1] segment sum
+    double cost = 0.0;                 // spread: relative duration
     int64_t blocks[2] = {0, 0};
     SpreadTable spread{};              // class tables (kernel arguments)
     EpilogueTable epi{};
@@ -470,19 +488,34 @@ int cellrun_parts(int rounds, bool small_plan, int64_t L, int64_t plan_waves)
 }
 
 // Automatic spreader: cell runs, unless the time series spends fewer than
-// kCellRunMinDensity samples in each cell it visits AND the spreader's LDS
-// leaves fewer than five workgroups per compute unit (sparse runs pay more
-// for the run search and partly used quads than they save, and that
-// search's dependent chain needs resident waves to hide behind).  The
-// density bar is lower in plans with at least 4096 instances: measured on
-// the beta bank (8280 instances, 12.8 samples per cell, n = 1200) cell runs
-// with four waves per instance take 1.01 ms per step against 1.11 ms for
-// sample runs, while on the 512-instance ragged batch the same switch for its
-// 12.8-sample classes costs 0.318 -> 0.350 ms.
-constexpr double kCellRunMinDensity = 24.0;
-constexpr double kCellRunMinDensityLarge = 12.0;
+// kCellRunMinDensity samples in each cell it visits (most lanes of a round
+// would have no sample).  FP64 classes without records whose grid copies leave
+// fewer than five workgroups a compute unit need more of them.  Measured, sample
+// runs against cell runs in us, 30 s on 1200 cells: 512 FP32 instances of 64 Hz
+// (1.6 samples a cell) 84 / 30, of 1024 Hz 78 / 45; 16384 of 64 Hz 1123 / 417;
+// FP64 with records, 512 of 256 Hz 97 / 53; without, 16384 of 64 Hz 918 / 1116,
+// of 256 Hz (6.4) 1584 / 1422, and on 2400 cells 4096 of 128 Hz (3.2) 959 /
+// 1077, of 256 Hz 1275 / 1200.
+constexpr double kCellRunMinDensity = 1.5;
+constexpr double kCellRunMinDensityFp64 = 4.0;
+// FP32 classes behind FP64 outputs keep the choice that they were given when
+// cell runs cost more LDS additions than they do (see free_order).
+constexpr double kKeptMinDensity = 24.0;
+constexpr double kKeptMinDensityLarge = 12.0;
 constexpr int64_t kLargePlanWaves = 4096;
 constexpr size_t kCellRunMaxSparseLds = kLdsBytes / 5;
+// Records instead of partial grids (the cell-run kernel says what they are), in
+// plans of fewer than kLargePlanWaves waves: on grids of kRecordMinGrid cells
+// and more, and on smaller ones only while the plan is a matter of latency
+// alone (120 cells, a record's 71 cells a round outweigh the grid: 512 instances
+// of 256 Hz 32 us with records, 26 with grids; one of them 22 against 24).
+// Sparse FP64 classes up to kRecordSparseWaves (30 s of 64 Hz on 1200 cells,
+// sample runs against records: 512 instances 79 / 51, 2048 139 / 163).
+constexpr int kRecordMinGrid = 256;
+constexpr int64_t kRecordFewWaves = 256;
+constexpr int64_t kRecordSparseWaves = 1024;
+// Most samples per cell that one wave with a record takes.
+constexpr double kRecordRunSamples = 32.0;
 // Longest heterodyne phase span, in phase-table steps, of an FP64 instance on
 // the fused spreaders (half the range of their 32-bit table-step conversion;
 // FP32 classes have no table and no such limit).
@@ -504,7 +537,7 @@ int small_plan_parts(int64_t L)
 }
 
 struct ClassKey {
-    int fp64, w, n, parts, method, flush, snap, radix, node_w;
+    int fp64, w, n, parts, method, flush, snap, radix, node_w;   // parts 0: records
     bool operator<(const ClassKey& o) const
     {
         return std::tie(fp64, w, n, parts, method, flush, snap, radix, node_w) <
@@ -1054,7 +1087,7 @@ bool plan_nodes(nr_plan_s& P)
 // Build the plan; nodes: instances that can take the node path do.  False
 // (with nodes only) if the sample path serves the plan better or the node
 // path does not fit the workspace: the plan is then half built.
-bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs, const nr_template* tmpls,
+bool build_plan(nr_plan_s& P, bool nodes, bool records, const nr_segment* segs, int32_t n_segs, const nr_template* tmpls,
                 int32_t n_tmpls, const nr_instance* inst, int64_t n_inst, double tol)
 {
     const nr_options& o = P.opt;
@@ -1104,6 +1137,7 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
             fail(NR_ERR_TOL_UNATTAINABLE, "instance " + std::to_string(i) + ": tol below 1e-12");
     }
 
+    bool any_records = false;
     std::map<ClassKey, size_t> class_of;
     std::map<ClassKey, double> class_tol;
     // largest grid whose spreader LDS (grids plus phase table) fits a workgroup
@@ -1177,11 +1211,15 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
             fail(NR_ERR_INVALID_ARG, "instance " + std::to_string(i) + ": grid size " + std::to_string(n) +
                                          " exceeds the supported maximum " + std::to_string(n_max) +
                                          " (lower n_bins or sigma)");
+        // FP32 classes behind FP64 outputs keep the spreader, and with it the
+        // order of additions, that they have always had: a program may compare
+        // such outputs far below the rounding of the sums behind them
+        const bool free_order = fp64 || !P.out_fp64;
         // tau series of the instance (ndeg < 0: the log1p/expm1 form)
         const double df_i = t.df > 0.0 ? t.df : g.fs / (double)g.n_samples;
         series.clear();
         int ndeg = 0;
-        int node_w = nodes ? node_width(fp64, w) : 0;
+        int node_w = nodes && free_order ? node_width(fp64, w) : 0;
         NodePick pick{};
         double y_ext = 0.0;
         if (node_w && !pick_nodes(h, g, t, df_i, fp64, node_w, &pick, &y_ext)) node_w = 0;
@@ -1228,17 +1266,30 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
         }
         int method = resolve_method(o.method);
         if (node_w) method = NR_METHOD_CELLRUN;
-        if (o.method == NR_METHOD_AUTO && !node_w &&
-            ((double)g.n_samples >= (small_plan && plan_waves < kLargePlanWaves ? kCellRunMinDensity
-                                                                                : kCellRunMinDensityLarge) *
-                                        cells_visited(h, g.n_samples, n, df_i) ||
-             spread_lds_bytes(fp64, n) <= kCellRunMaxSparseLds))
-            method = NR_METHOD_CELLRUN;
+        // records need every class in one chunk; a plan of kLargePlanWaves or
+        // more fills the GPU with fewer waves and runs the fused epilogue
+        const bool rec_plan = records && free_order && small_plan && plan_waves < kLargePlanWaves &&
+                              (n >= kRecordMinGrid || plan_waves < kRecordFewWaves);
+        const double visited = cells_visited(h, g.n_samples, n, df_i);
+        const double density = (double)g.n_samples / visited;
+        if (o.method == NR_METHOD_AUTO && !node_w) {
+            const bool lean = spread_lds_bytes(fp64, n) <= kCellRunMaxSparseLds;
+            if (!free_order)
+                method = density >= (small_plan && plan_waves < kLargePlanWaves ? kKeptMinDensity : kKeptMinDensityLarge) ||
+                                 lean ? NR_METHOD_CELLRUN : method;
+            else if (density >= kCellRunMinDensity &&
+                     (!fp64 || (rec_plan && plan_waves < kRecordSparseWaves) || lean ||
+                      density >= kCellRunMinDensityFp64))
+                method = NR_METHOD_CELLRUN;
+        }
         int parts = o.parts ? o.parts : small_plan ? small_plan_parts(g.n_samples) : default_parts(g.n_samples);
+        bool rec = false;
         if (node_w)
             parts = 1;
-        else if (method == NR_METHOD_CELLRUN && o.parts == 0)
-            parts = cellrun_parts(cellrun_rounds(h, g.n_samples, n, df_i), small_plan, g.n_samples, plan_waves);
+        else if (method == NR_METHOD_CELLRUN && o.parts == 0) {
+            rec = rec_plan && density >= kCellRunMinDensity && visited < 4e6;
+            parts = rec ? 0 : cellrun_parts(cellrun_rounds(h, g.n_samples, n, df_i), small_plan, g.n_samples, plan_waves);
+        }
         int flush = o.flush_period;
         int snap = o.moment_mode == 2 ? 1 : 0;
         int radix = P.radix_override;
@@ -1267,6 +1318,11 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
         // (FP32 classes: phase_steps is 0, they have no table)
         if (phase_steps >= kFusedMaxPhaseSteps && method != NR_METHOD_DIRECT && !node_w) method = NR_METHOD_STAGED;
         if (method == NR_METHOD_CELLRUN) snap = 0;  // moments restart with every run
+        if (rec && method != NR_METHOD_CELLRUN) {
+            rec = false;
+            parts = small_plan_parts(g.n_samples);
+        }
+        any_records = any_records || rec;
         ClassKey key{fp64, w, n, parts, method, flush, snap, radix, node_w};
         size_t ci;
         const bool same = !(key < last_key) && !(last_key < key);
@@ -1297,6 +1353,11 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
         last_key = key;
         last_ci = ci;
         Class& c = *P.classes[ci];
+        if (rec) {
+            c.rec_stride = kWave + w - 1;
+            c.rounds = std::max(c.rounds, cellrun_rounds(h, g.n_samples, n, df_i));
+            c.run_samples = std::max(c.run_samples, (double)g.n_samples / cells_visited(h, g.n_samples, n, df_i));
+        }
         InstDev d{};
         const double df = t.df > 0.0 ? t.df : g.fs / (double)g.n_samples;
         d.df = df;
@@ -1324,6 +1385,19 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
         c.n_points += g.n_samples;
     }
     if (nodes && !plan_nodes(P)) return false;
+    if (nodes && o.max_workspace_bytes > 0) {
+        // a cap that has the sample path split its grids into chunks means
+        // that: the node path would hold the values of every segment at once
+        int64_t grids = 0;
+        for (auto& cp : P.classes) grids += (int64_t)cp->inst.size() * cp->n * (cp->fp64 ? 16 : 8);
+        if (grids > o.max_workspace_bytes / 2) return false;
+    }
+    for (auto& cp : P.classes) {
+        Class& c = *cp;
+        if (!c.rec_stride) continue;
+        while (c.rec_shift < 4 && c.run_samples > kRecordRunSamples * (double)(1 << c.rec_shift)) ++c.rec_shift;
+        c.parts = ((c.rounds << c.rec_shift) + 3) / 4 * 4;
+    }
     for (auto& kv : class_of) build_class_tables(*P.classes[kv.second], class_tol[kv.first], sigma);
 
     // Lane-major strain layout per class, point-stream offsets, templates
@@ -1396,9 +1470,7 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
             for (int32_t k : lists[t]) ct_of[k] = (int32_t)t;
         fixed_bytes += c.strain_entries * esize;
         // chunks bounded by the workspace cap
-        // the direct baseline and the node classes need no grid
-        const int64_t gsize =
-            c.method == NR_METHOD_DIRECT || c.node_w ? 0 : (int64_t)c.n * (c.fp64 ? 16 : 8) * grid_slots(c.parts);
+        const int64_t gsize = grid_bytes(c);
         const int64_t psz = c.method == NR_METHOD_STAGED ? (c.fp64 ? psize_d : psize_f) : 0;
         const int64_t budget = std::max<int64_t>(cap / 2, 1);
         int64_t k0 = 0;
@@ -1434,7 +1506,7 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
         {
             const bool wanted =
                 (o.epilogue == 0 && (!small_plan || plan_waves >= kLargePlanWaves)) || o.epilogue == 2;
-            const bool fits = c.method != NR_METHOD_DIRECT && c.parts <= 4 &&
+            const bool fits = c.method != NR_METHOD_DIRECT && !c.rec_stride && c.parts <= 4 &&
                               lds_tier(spread_lds_bytes(c.fp64, c.n, c.parts == 1)) >=
                                   lds_tier(spread_lds_bytes(c.fp64, c.n, 0));
             c.fuse_epi = (wanted && fits) || c.node_w ? 1 : 0;
@@ -1460,7 +1532,8 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
                                  c.d_tmpl_list.bytes + c.d_tmpl_list_off.bytes + c.d_tmpl_stat_off.bytes +
                                  c.d_entry_seg.bytes + c.d_order.bytes + c.d_dft.bytes);
     }
-    if (nodes && fixed_bytes + grid_chunk_bytes + point_chunk_bytes > cap) return false;
+    const bool retry = nodes || any_records;
+    if (retry && fixed_bytes + grid_chunk_bytes + point_chunk_bytes > cap) return false;
     if (fixed_bytes + grid_chunk_bytes + point_chunk_bytes > cap)
         fail(NR_ERR_OUT_OF_MEMORY, "workspace of " + std::to_string(fixed_bytes + grid_chunk_bytes + point_chunk_bytes) +
                                        " bytes exceeds max_workspace_bytes " + std::to_string(cap));
@@ -1470,6 +1543,7 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
         one_chunk = one_chunk && cp->chunks.size() <= 1;
         any_direct = any_direct || cp->method == NR_METHOD_DIRECT;
     }
+    if (any_records && (!one_chunk || grid_total + point_total > std::max<int64_t>(cap / 2, 1))) return false;
     P.batched = P.classes.size() > 1 && one_chunk && !any_direct && fixed_bytes + grid_total + point_total <= cap &&
                 grid_total + point_total <= std::max<int64_t>(cap / 2, 1);
     if (P.batched) {
@@ -1478,8 +1552,7 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
             Class& c = *cp;
             c.grid_off = go;
             c.pts_off = po;
-            const int64_t gsize = c.node_w ? 0 : (int64_t)c.n * (c.fp64 ? 16 : 8) * grid_slots(c.parts);
-            go += (int64_t)c.inst.size() * gsize;
+            go += (int64_t)c.inst.size() * grid_bytes(c);
             if (c.method == NR_METHOD_STAGED)
                 po += c.pt_entries * (c.fp64 ? (int64_t)psize_d : (int64_t)psize_f);
             go = (go + 255) & ~int64_t(255);
@@ -1500,7 +1573,7 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
         P.two_pass = one_chunk && !P.classes.empty() &&
                      fixed_bytes + grid_chunk_bytes + point_chunk_bytes + rbytes <= cap;
         // node classes write power rows: without them the sample path takes over
-        if (nodes && !P.two_pass) return false;
+        if (retry && !P.two_pass) return false;
         if (P.two_pass) P.d_rows.alloc((size_t)rbytes, "power rows");
         if (any_direct && !P.two_pass)
             fail(NR_ERR_OUT_OF_MEMORY, "the direct method needs every class in one chunk with its power rows "
@@ -1546,6 +1619,10 @@ bool build_plan(nr_plan_s& P, bool nodes, const nr_segment* segs, int32_t n_segs
     return true;
 }
 
+// Records need the automatic waves per instance and room that the caller's
+// arena was not sized for.
+bool records_allowed(const nr_options& o) { return o.parts == 0 && !o.tune && o.epilogue != 2 && !g_arena; }
+
 // Options that leave the spreader to the plan and real strain: the node path
 // may serve the plan.  The static-scratch entry point plans on every call and
 // keeps the sample path, whose plan is shorter.
@@ -1558,18 +1635,22 @@ bool nodes_allowed(const nr_options& o, int radix_override)
 void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_template* tmpls,
                  int32_t n_tmpls, const nr_instance* inst, int64_t n_inst, double tol)
 {
-    if (nodes_allowed(P.opt, P.radix_override)) {
+    const bool nodes = nodes_allowed(P.opt, P.radix_override), records = records_allowed(P.opt);
+    for (int level = 0; level < 2; ++level) {
+        if (!(level ? records : nodes)) continue;
         try {
-            if (build_plan(P, true, segs, n_segs, tmpls, n_tmpls, inst, n_inst, tol)) return;
+            if (build_plan(P, level == 0, records, segs, n_segs, tmpls, n_tmpls, inst, n_inst, tol)) return;
         } catch (const NrError& e) {
             if (e.code != NR_ERR_OUT_OF_MEMORY) throw;
         }
         const nr_options o = P.opt;
+        const int radix = P.radix_override;
         P.~nr_plan_s();
         new (&P) nr_plan_s();
         P.opt = o;
+        P.radix_override = radix;
     }
-    build_plan(P, false, segs, n_segs, tmpls, n_tmpls, inst, n_inst, tol);
+    build_plan(P, false, false, segs, n_segs, tmpls, n_tmpls, inst, n_inst, tol);
 }
 
 // ------------------------------------------------------------ execution --
@@ -1628,6 +1709,8 @@ SpreadArgs spread_args(const nr_plan_s& P, const Class& c, const Chunk& ch)
     a.fft.n = c.n;
     a.fft.nr = (int32_t)c.radix.size();
     for (size_t r = 0; r < c.radix.size(); ++r) a.fft.radix[r] = c.radix[r];
+    a.rec_stride = c.rec_stride;
+    a.rec_shift = c.rec_shift;
     a.block_order = ch.order_off >= 0 ? (const int32_t*)c.d_order.p + ch.order_off : nullptr;
     return a;
 }
@@ -1651,6 +1734,9 @@ EpilogueArgs epilogue_args(const nr_plan_s& P, const Class& c, const Chunk& ch)
     e.tmpl_first = ch.tmpl_first;
     e.tmpl_count = ch.tmpl_count;
     e.slots = grid_slots(c.parts);
+    e.parts = c.parts;
+    e.rec_stride = c.rec_stride;
+    e.rec_shift = c.rec_shift;
     e.kmax = c.kmax;
     e.row_base = c.row_base;
     e.entry_seg = (const int32_t*)c.d_entry_seg.p;
@@ -1689,8 +1775,10 @@ NodeArgs node_args(const nr_plan_s& P, const Class& c)
 
 void build_groups(nr_plan_s& P)
 {
-    // spread: same kernel instantiation and LDS tier
-    std::map<std::array<int, 5>, size_t> sg;
+    // spread: same kernel instantiation, and the same LDS tier unless every
+    // workgroup is resident at once in the lower one (512 ragged instances: 10
+    // spread launches on four streams took 145 us, 5 take 100)
+    std::map<std::array<int, 4>, std::vector<size_t>> sg;
     // epilogue groups: a segment sum adds into its templates' statistics
     // without atomics, so the classes of one group have disjoint templates
     std::map<std::array<int, 3>, std::vector<size_t>> eg;
@@ -1702,16 +1790,23 @@ void build_groups(nr_plan_s& P)
         const int snap = (c.snap && !c.fp64 && c.deg <= 12) ? 1 : 0;
         // fused and separate-epilogue classes share launches (the flag is per
         // class in the launch table); their epilogue groups stay apart
-        const size_t sl = spread_lds_bytes(c.fp64, c.n, c.fuse_epi && c.parts == 1);
-        const std::array<int, 5> sk{c.fp64, c.deg, fused, snap, lds_tier(sl)};
-        auto it = sg.find(sk);
-        // node classes are launched one by one
-        if (it != sg.end() && (c.node_w || P.spread_groups[it->second].cls.size() >= (size_t)kGroupMax)) {
-            sg.erase(it);    // full: later classes of this kind start a new group
-            it = sg.end();
+        const size_t sl = class_lds(c);
+        const int64_t blocks = spread_blocks(c.chunks[0].count, c.parts);
+        std::vector<size_t>& like = sg[{c.fp64, c.deg, fused, snap}];
+        size_t at = SIZE_MAX;
+        for (size_t q : like) {
+            const Group& g = P.spread_groups[q];
+            // node classes are launched one by one
+            if (c.node_w || g.cls.size() >= (size_t)kGroupMax) continue;
+            if (lds_tier(sl) == lds_tier(g.lds[0]) ||
+                g.blocks[0] + blocks <= (int64_t)kCus * lds_tier(std::max(sl, g.lds[0]))) {
+                at = q;
+                break;
+            }
         }
-        if (it == sg.end()) {
-            it = sg.emplace(sk, P.spread_groups.size()).first;
+        if (at == SIZE_MAX) {
+            at = P.spread_groups.size();
+            like.push_back(at);
             P.spread_groups.emplace_back();
             Group& g = P.spread_groups.back();
             g.fp64 = c.fp64;
@@ -1719,8 +1814,16 @@ void build_groups(nr_plan_s& P)
             g.fused = fused;
             g.snap = snap;
         }
-        Group& g = P.spread_groups[it->second];
+        Group& g = P.spread_groups[at];
+        g.blocks[0] += blocks;
         g.cls.push_back((int)ci);
+        // a launch lasts as long as one lane's samples take (a step of a sample
+        // run 2 us with its flushes, a sample of a cell run about 0.3 us), and a
+        // few us besides
+        for (const InstDev& d : c.inst) {
+            const double lane_samples = (double)d.L / ((double)kWave * std::max(1, c.parts));
+            g.cost = std::max(g.cost, 5.0 + lane_samples * (fused == 2 || fused == 3 ? 0.3 : 2.0));
+        }
         g.lds[0] = std::max(g.lds[0], sl);
         const size_t el = epilogue_lds_bytes(c.fp64, c.n, c.kmax, 1);
         const std::array<int, 3> ek{c.fp64, lds_tier(el), c.fuse_epi};
@@ -1761,6 +1864,9 @@ void build_groups(nr_plan_s& P)
         }
         g.blocks[0] = off;
     }
+    // longest first, each on the stream that is free first
+    std::stable_sort(P.spread_groups.begin(), P.spread_groups.end(),
+                     [](const Group& x, const Group& y) { return x.cost > y.cost; });
     for (Group& g : P.epi_groups) {
         int64_t off[2] = {0, 0};
         g.epi.ncls = (int32_t)g.cls.size();
@@ -1872,9 +1978,11 @@ void run_front_batched(nr_plan_s& P, const EpilogueOut& out)
 {
     const int ns = side_count(P, P.spread_groups.size());
     fork_side(P, 0, ns);
-    for (size_t gi = 0; gi < P.spread_groups.size(); ++gi) {
-        Group& g = P.spread_groups[gi];
-        hipStream_t st = lane_stream(P, gi, ns);
+    std::vector<double> busy((size_t)ns + 1, 0.0);
+    for (Group& g : P.spread_groups) {
+        const size_t lane = (size_t)(std::min_element(busy.begin(), busy.end()) - busy.begin());
+        busy[lane] += g.cost;
+        hipStream_t st = lane_stream(P, lane, ns);
         for (int ci : g.cls) {
             Class& c = *P.classes[ci];
             if (c.method != NR_METHOD_STAGED || c.chunks.empty()) continue;
