@@ -23,34 +23,103 @@ nr_status fail(const std::string& m, nr_status st)
     return st;
 }
 
-// One thread per fold slot r of segment blockIdx.y: the grid points r,
-// r + fold, ... < M.
-template <bool CPLX>
+// Value of a double in lane k (k the same in every lane).
+__device__ __forceinline__ double lane_value(double v, int k)
+{
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(b & 0xffffffffLL), k);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), k);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// PER fold slots a thread, r = r0 + p 256 + threadIdx.x of segment blockIdx.y:
+// the grid points r, r + fold, ... < M of each, in that order.
+//
+// The sample nearest to a grid point is rint of the inverse time map, whose
+// log1p and expm1 in FP64 bound the kernel (8 segments of 2^20 samples, a
+// million grid points each: 52 us; now 24).  The points of one workgroup and one
+// multiple of the fold lie close together, so one evaluation in their middle
+// (lane k does that for multiple k) serves them all: with z = d / (fs a y),
+// d the distance in points and y = 1 - tau / a in the middle, the map is
+// Q + G (1 - (1 - z)^1.6), G = fs tscale y^1.6, and the binomial series to z^4
+// is off by less than 0.02 G z^5.  That integer is the plain evaluation's
+// wherever the value lies further than both errors from a half-integer:
+// 1e-6 samples for the series (the middle is taken only if its bound is ten
+// times smaller) and 1e-14 of the value for roundings (the plain one takes
+// about ten operations of 2^-53 each).  Elsewhere, about two points in a
+// million, and where the series is not short enough, the plain evaluation
+// decides.
+template <bool CPLX, int PER>
 __global__ __launch_bounds__(256) void fold_kernel(const float* __restrict__ x, int64_t n, double fs_o, double a,
                                                    double tscale, int identity, int64_t M, int64_t fold,
                                                    float2* __restrict__ out)
 {
 #pragma clang fp contract(off)
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= fold) return;
+    const int64_t r0 = (int64_t)blockIdx.x * (256 * PER);
     x += (int64_t)blockIdx.y * n * (CPLX ? 2 : 1);
     out += (int64_t)blockIdx.y * fold;
-    float re = 0.0f, im = 0.0f;
-    for (int64_t m = r; m < M; m += fold) {
-        const double tau = (double)m / fs_o;
-        const double t = identity ? tau : -expm1(1.6 * log1p(-tau / a)) * tscale;
-        const double q = rint(t * fs_o);
-        if (q >= 0.0 && q < (double)n) {
-            const int64_t s = (int64_t)q;
-            if (CPLX) {
-                re += x[2 * s];
-                im += x[2 * s + 1];
-            } else {
-                re += x[s];
+    constexpr double kHalf = 128.0 * PER;
+    const int lane = threadIdx.x & 63;
+    const double A = tscale * fs_o;
+    float re[PER], im[PER];
+#pragma unroll
+    for (int p = 0; p < PER; ++p) re[p] = im[p] = 0.0f;
+    for (int64_t m0 = r0; m0 < M; m0 += 64 * fold) {
+        const double xm = ((double)(m0 + lane * fold) + kHalf) / fs_o / a;
+        const double E = expm1(1.6 * log1p(-xm));        // y^1.6 - 1
+        const double G = A * (1.0 + E), z1 = 1.0 / (fs_o * a * (1.0 - xm)), zm = kHalf * z1;
+        const bool near = !identity && zm > 0.0 && zm < 0.1 && 0.02 * G * zm * zm * zm * zm * zm < 1e-7;
+        const double mine = near ? z1 : NAN, Qm = -E * A;   // NAN: no comparison below holds
+        for (int k = 0; k < 64 && m0 + k * fold < M; ++k) {
+            const double zs = lane_value(mine, k), Q = lane_value(Qm, k), g = lane_value(G, k);
+#pragma unroll
+            for (int p = 0; p < PER; ++p) {
+                const int at = p * 256 + threadIdx.x;
+                const int64_t m = m0 + k * fold + at;
+                if (r0 + at >= fold || m >= M) continue;
+                const double z = ((double)at - kHalf) * zs;
+                const double v = fma(g, z * fma(z, -fma(z, fma(z, 0.0224, 0.064), 0.48), 1.6), Q);
+                double q = rint(v);
+                if (!(fabs(v - q) < 0.5 - 1e-6 - 1e-14 * fabs(v))) {
+                    const double tau = (double)m / fs_o;
+                    const double t = identity ? tau : -expm1(1.6 * log1p(-tau / a)) * tscale;
+                    q = rint(t * fs_o);
+                }
+                if (q >= 0.0 && q < (double)n) {
+                    const int64_t s = (int64_t)q;
+                    if (CPLX) {
+                        re[p] += x[2 * s];
+                        im[p] += x[2 * s + 1];
+                    } else {
+                        re[p] += x[s];
+                    }
+                }
             }
         }
     }
-    out[r] = make_float2(re, im);
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const int64_t r = r0 + p * 256 + threadIdx.x;
+        if (r < fold) out[r] = make_float2(re[p], im[p]);
+    }
+}
+
+// Slots a thread: eight, to share one evaluation among 2048 points, where that
+// leaves two workgroups a compute unit.
+constexpr int kSlots = 8;
+constexpr int64_t kManyBlocks = 512;
+
+template <bool CPLX>
+void launch_fold(const float* x, int64_t n, int32_t n_seg, double fs_o, double a, double tscale, int identity,
+                 int64_t M, int64_t fold, float2* out, hipStream_t st)
+{
+    const int64_t many = (fold + 256 * kSlots - 1) / (256 * kSlots);
+    if (many * n_seg >= kManyBlocks)
+        fold_kernel<CPLX, kSlots><<<dim3((unsigned)many, (unsigned)n_seg), 256, 0, st>>>(x, n, fs_o, a, tscale,
+                                                                                       identity, M, fold, out);
+    else
+        fold_kernel<CPLX, 1><<<dim3((unsigned)((fold + 255) / 256), (unsigned)n_seg), 256, 0, st>>>(
+            x, n, fs_o, a, tscale, identity, M, fold, out);
 }
 
 // The grid of the segment: M and the constants of the inverse time map.
@@ -104,14 +173,11 @@ nr_status nr_strobo_fold(const void* x, int32_t x_complex, int64_t n_samples, in
     Grid g{};
     const nr_status st = make_grid(fs_o, n_samples, mc_msun, f0, g);
     if (st != NR_OK) return st;
-    const dim3 blocks((unsigned)((fold + 255) / 256), (unsigned)n_seg);
     hipStream_t s = (hipStream_t)stream;
     if (x_complex)
-        fold_kernel<true><<<blocks, 256, 0, s>>>((const float*)x, n_samples, fs_o, g.a, g.tscale, g.identity, g.M,
-                                                 fold, (float2*)out);
+        launch_fold<true>((const float*)x, n_samples, n_seg, fs_o, g.a, g.tscale, g.identity, g.M, fold, (float2*)out, s);
     else
-        fold_kernel<false><<<blocks, 256, 0, s>>>((const float*)x, n_samples, fs_o, g.a, g.tscale, g.identity, g.M,
-                                                  fold, (float2*)out);
+        launch_fold<false>((const float*)x, n_samples, n_seg, fs_o, g.a, g.tscale, g.identity, g.M, fold, (float2*)out, s);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(std::string("fold: ") + hipGetErrorString(e), NR_ERR_DEVICE);
     return NR_OK;
