@@ -23,6 +23,7 @@ thread_local std::string g_ss_error;
 constexpr int kWave = 64;
 constexpr int kBlock = 256;
 constexpr int kTile = 32;
+constexpr int kAhead = 8;     // power values in flight per lane
 
 // One lag of one (chirp mass, start offset) track family.
 struct SsEntry {
@@ -37,6 +38,15 @@ __device__ __forceinline__ int64_t uniform64(int64_t v)
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
     return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// Value of a double in lane k (k the same in every lane).
+__device__ __forceinline__ double lane_value(double v, int k)
+{
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(b & 0xffffffffLL), k);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), k);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
 // Track tables: one thread per (chirp mass c, start offset s) walks the lags
@@ -85,8 +95,13 @@ __global__ void tables_kernel(const double* __restrict__ beta_start, const doubl
 }
 
 // One wave per (chirp mass, start offset, 64 consecutive start segments i0):
-// the lags' table entries are the same for every lane (scalar loads), and in
-// layout 1 the lanes read 64 consecutive segments of one (template, bin).
+// the lags' table entries are the same for every lane, and in layout 1 the
+// lanes read 64 consecutive segments of one (template, bin).  A track's entries
+// are read by no other family: as scalar loads, a line every third lag, their
+// latencies and those of the power values behind them were the launch.  Now the
+// lanes load 64 lags' entries at once, hand them round by lane reads, and
+// kAhead power values are on their way together.  2048 chirp masses x 8 starts
+// x 120 segments: 131 -> 116 us, 500 x 4 in layout 0 48 -> 34.
 // ACC: only the segments of [seg_lo, seg_hi) take part, the power buffer
 // holds exactly those (segment i at position i - seg_lo, n_buf = seg_hi -
 // seg_lo of them), and out and used are accumulated into (+=).  The weights
@@ -117,16 +132,30 @@ __global__ __launch_bounds__(kBlock) void gather_kernel(const float* __restrict_
     const int m_hi = min(min(M, n_seg - chunk * kWave), hi - chunk * kWave);
     double acc = 0.0;
     int cnt = 0;
-#pragma unroll 4
-    for (int m = m_lo; m < m_hi; ++m) {
-        const int k = row[m].k, j = row[m].j;
-        const double w = row[m].w;
-        const int i = i0 + m;
-        if (m < lim && (!ACC || (i >= lo && i < hi))) {
-            const int64_t idx = LAYOUT == 0 ? ((int64_t)k * n_buf + (i - lo)) * n_bins + j
-                                            : ((int64_t)k * n_bins + j) * n_buf + (i - lo);
-            acc += w * (a * (double)P[idx] - b);
-            if (ACC) ++cnt;
+    for (int mb = m_lo; mb < m_hi; mb += kWave) {
+        const int here = min(kWave, m_hi - mb);
+        const SsEntry* __restrict__ e = row + mb + min(lane, here - 1);
+        const int ek = e->k, ej = e->j;
+        const double ew = e->w;
+        for (int t0 = 0; t0 < here; t0 += kAhead) {
+            float pv[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int t = min(t0 + u, here - 1);
+                const int64_t k = __builtin_amdgcn_readlane(ek, t), j = __builtin_amdgcn_readlane(ej, t);
+                // lanes without this lag read a neighbour's segment and drop it
+                const int i = min(max(i0 + mb + t, lo), hi - 1) - lo;
+                pv[u] = LAYOUT == 0 ? P[(k * n_buf + i) * n_bins + j] : P[(k * n_bins + j) * n_buf + i];
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int m = mb + t0 + u, i = i0 + m;
+                const double w = lane_value(ew, min(t0 + u, here - 1));
+                const bool in = t0 + u < here && m < lim && (!ACC || (i >= lo && i < hi));
+                const double v = acc + w * (a * (double)pv[u] - b);
+                acc = in ? v : acc;
+                if (ACC) cnt += in;
+            }
         }
     }
     if (i0 < n_seg) {
