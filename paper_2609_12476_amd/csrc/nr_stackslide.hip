@@ -49,6 +49,12 @@ __device__ __forceinline__ double lane_value(double v, int k)
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int k) { return __builtin_amdgcn_readlane(v, k); }
+__device__ __forceinline__ uint64_t lane_value(uint64_t v, int k)
+{
+    return (uint64_t)__double_as_longlong(lane_value(__longlong_as_double((long long)v), k));
+}
+
 // Track tables: one thread per (chirp mass c, start offset s) walks the lags
 // m = 0, 1, ... of the tracks t0 = (i0 - s/S) t_coh; lag m is the segment
 // (m + s/S) t_coh after t0.  The arithmetic that decides integers (end of
@@ -101,14 +107,16 @@ __global__ void tables_kernel(const double* __restrict__ beta_start, const doubl
 // latencies and those of the power values behind them were the launch.  Now the
 // lanes load 64 lags' entries at once, hand them round by lane reads, and
 // kAhead power values are on their way together.  2048 chirp masses x 8 starts
-// x 120 segments: 131 -> 116 us, 500 x 4 in layout 0 48 -> 34.
+// x 120 segments: 131 -> 83 us, 500 x 4 in layout 0 48 -> 33.  What bounds it now
+// is the issue of about 16 vector and 8 scalar instructions a lag; with every
+// address in 64-bit scalar arithmetic (21 scalar ones) it took 116.
 // ACC: only the segments of [seg_lo, seg_hi) take part, the power buffer
 // holds exactly those (segment i at position i - seg_lo, n_buf = seg_hi -
 // seg_lo of them), and out and used are accumulated into (+=).  The weights
 // are normalised over the whole track, so the partial sums of consecutive
 // segment ranges add up to the statistic of the whole track.  Otherwise the
 // buffer holds every segment and out and used are written.
-template <int LAYOUT, bool ACC>
+template <int LAYOUT, bool ACC, typename Off>
 __global__ __launch_bounds__(kBlock) void gather_kernel(const float* __restrict__ P, const SsEntry* __restrict__ tab,
                                                         const int32_t* __restrict__ len, int64_t n_fam, int S,
                                                         int n_seg, int n_bins, int chunks, int seg_lo, int seg_hi,
@@ -135,26 +143,35 @@ __global__ __launch_bounds__(kBlock) void gather_kernel(const float* __restrict_
     for (int mb = m_lo; mb < m_hi; mb += kWave) {
         const int here = min(kWave, m_hi - mb);
         const SsEntry* __restrict__ e = row + mb + min(lane, here - 1);
-        const int ek = e->k, ej = e->j;
         const double ew = e->w;
+        const Off at = LAYOUT == 0 ? ((Off)e->k * n_buf * n_bins + e->j) * 4 : ((Off)e->k * n_bins + e->j) * n_buf * 4;
+        const Off step = (Off)(LAYOUT == 0 ? n_bins : 1) * 4;
         for (int t0 = 0; t0 < here; t0 += kAhead) {
             float pv[kAhead];
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
+                // lags past the last are its repeats; lanes without this lag
+                // read a neighbour's segment: both are dropped below
                 const int t = min(t0 + u, here - 1);
-                const int64_t k = __builtin_amdgcn_readlane(ek, t), j = __builtin_amdgcn_readlane(ej, t);
-                // lanes without this lag read a neighbour's segment and drop it
-                const int i = min(max(i0 + mb + t, lo), hi - 1) - lo;
-                pv[u] = LAYOUT == 0 ? P[(k * n_buf + i) * n_bins + j] : P[(k * n_bins + j) * n_buf + i];
+                int i = min(i0 + mb + t, hi - 1);
+                if (ACC) i = max(i, lo) - lo;
+                pv[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(P) +
+                                                        (lane_value(at, t) + (Off)i * step));
             }
+            // lags below 'left' are this lane's
+            const int left = min(lim, m_hi) - (mb + t0);
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
-                const int m = mb + t0 + u, i = i0 + m;
                 const double w = lane_value(ew, min(t0 + u, here - 1));
-                const bool in = t0 + u < here && m < lim && (!ACC || (i >= lo && i < hi));
                 const double v = acc + w * (a * (double)pv[u] - b);
-                acc = in ? v : acc;
-                if (ACC) cnt += in;
+                if (ACC) {
+                    const int i = i0 + mb + t0 + u;
+                    const bool in = u < left && i >= lo && i < hi;
+                    acc = in ? v : acc;
+                    cnt += in;
+                } else {
+                    acc = u < left ? v : acc;
+                }
             }
         }
     }
@@ -243,14 +260,25 @@ nr_status gather(nr_ss_plan p, const float* power, int32_t seg_begin, int32_t se
     const unsigned blocks = (unsigned)((waves * kWave + kBlock - 1) / kBlock);
     const double a = g.norm / g.sigma, b = g.mu / g.sigma;
     const int lo = seg_begin, hi = seg_begin + seg_count;
-#define NR_GATHER(LAY, ACC)                                                                                          \
-    gather_kernel<LAY, ACC><<<blocks, kBlock, 0, p->stream>>>(power, p->tab, p->len, fam, p->S, g.n_seg, g.n_bins, \
+    // byte offsets into the power buffer in 32 bits where they fit
+    const bool wide = (double)g.n_beta * g.n_bins * seg_count * 4.0 >= 4294967296.0;
+#define NR_GATHER(LAY, ACC, OFF)                                                                                         \
+    gather_kernel<LAY, ACC, OFF><<<blocks, kBlock, 0, p->stream>>>(power, p->tab, p->len, fam, p->S, g.n_seg, g.n_bins, \
                                                               chunks, lo, hi, a, b, n_sigma, n_used)
-    if (g.layout == 0) {
-        if (acc) NR_GATHER(0, true); else NR_GATHER(0, false);
-    } else {
-        if (acc) NR_GATHER(1, true); else NR_GATHER(1, false);
+#define NR_GATHER_L(LAY)                                        \
+    if (wide) {                                                 \
+        if (acc) NR_GATHER(LAY, true, uint64_t);                \
+        else NR_GATHER(LAY, false, uint64_t);                   \
+    } else {                                                    \
+        if (acc) NR_GATHER(LAY, true, uint32_t);                \
+        else NR_GATHER(LAY, false, uint32_t);                   \
     }
+    if (g.layout == 0) {
+        NR_GATHER_L(0)
+    } else {
+        NR_GATHER_L(1)
+    }
+#undef NR_GATHER_L
 #undef NR_GATHER
     return device_status(p, hipGetLastError(), "stack-slide");
 }
