@@ -117,6 +117,19 @@ def algorithmic_ops(classes):
     return tot
 
 
+def node_ops(classes, nodes):
+    """VALU lane-operations the node spreader needs: per node the tau series
+    (degree + 1 FMAs), 8 for the grid position and its split, 13 for the sin/cos
+    pair of the carrier, 4 for its product with the node's value, the kernel's
+    width values (half of them by the degree-`degree` pieces of their even and
+    odd parts: (degree + 1) + 1 each) and 2 per cell for the complex sums."""
+    tot = 0.0
+    for c, q in zip(classes, nodes):
+        terms = c.series_terms / max(c.n_points, 1)
+        tot += q.nodes * (terms + 1 + 8 + 13 + 4 + q.width * (q.degree + 2) + 2 * q.width)
+    return tot
+
+
 def spread_fft_bytes(classes, strain_bytes, stat_bins, K):
     """Algorithmic HBM bytes of the spread, FFT and segment-sum stages of one
     step: the strain once, the point stream of staged classes (read by the
@@ -224,7 +237,7 @@ def measure_workload(args, dev, workload, steps, check=16, tune=False, method="a
             pstep()
         stt = prof.stage_times()
         spread_ms = stt["spread"][0] / steps
-        if all(c.method in (2, 3) for c in cls):
+        if all(c.method in (2, 3) for c in cls) and not any(q.width for q in prof.nodes()):
             ops = algorithmic_ops(cls)
             out["spread_ms_per_step"] = spread_ms
             out["spread_valu_frac"] = ops / (spread_ms * 1e-3) / 1e12 / VALU_PEAK_TOPS
@@ -612,6 +625,7 @@ def main():
     launches = st[dom][1] / args.steps
     per_launch_ms = stage_ms[dom] / max(launches, 1)
     n = cls[0].n
+    nodes = plan.nodes()
     pts = info.valid_points
     if dom == "spread" and args.method == "staged":
         bytes_step = pts * 8 + info.n_valid * n * 8           # point stream in, grid out
@@ -625,6 +639,20 @@ def main():
         roof = {"kernel": "tau_kernel<float>", "bound": "hbm", "achieved": achieved,
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                 "traffic": None}
+    elif dom == "spread" and any(q.width for q in nodes):
+        ops = node_ops(cls, nodes)
+        achieved = ops / max(launches, 1) / (per_launch_ms * 1e-3) / 1e12
+        kname = "nr::node_spread_dft_kernel<float>"
+        roof = {"kernel": kname, "bound": "alu", "achieved": achieved,
+                "peak": VALU_PEAK_TOPS, "unit": "TOP/s", "frac": achieved / VALU_PEAK_TOPS,
+                "traffic": committed_traffic(kname) if len(cls) == 1 else None,
+                "traffic_unit": "bytes per launch", "ops_per_node": ops / sum(q.nodes for q in nodes),
+                "achieved_basis": "algorithmic VALU lane-operations of the per-node op model (node_ops) over the "
+                                  "HIP-event launch time; peak = 256 CU x 64 lanes x 2.4 GHz, one FP32 or FP64 FMA "
+                                  "per lane per cycle"}
+        vi = committed_counter(kname, "valu_instructions_per_launch") if len(cls) == 1 else None
+        if vi is not None:
+            roof["valu_issue_frac_counters"] = vi * 4 / (1024 * 2.4e9 * per_launch_ms * 1e-3)
     elif dom == "spread":
         ops = algorithmic_ops(cls)
         achieved = ops / max(launches, 1) / (per_launch_ms * 1e-3) / 1e12

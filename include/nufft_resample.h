@@ -81,10 +81,12 @@ typedef enum {
     NR_METHOD_AUTO = 0,   /* band-limited nodes where the plan's templates share segments
                              (nr_node_info); otherwise per instance
                              NR_METHOD_CELLRUN when its time series spends
-                             at least 24 samples (12 in plans of 4096 or more
-                             instances) in each grid cell it visits or its
-                             spreader workgroup needs at most 1/5 of a compute unit's
-                             LDS; else NR_METHOD_FUSED */
+                             at least 1.5 samples in each grid cell it visits (4 in
+                             FP64 classes of large plans whose spreader workgroup needs
+                             more than 1/5 of a compute unit's LDS); else
+                             NR_METHOD_FUSED.  FP32 classes behind FP64 outputs
+                             (NR_AUTO): no nodes, and cell runs from 24 samples on (12
+                             in plans of 4096 or more instances) or within that LDS */
     NR_METHOD_STAGED = 1, /* tau kernel writes a point stream; spreader reads it */
     NR_METHOD_FUSED = 2,  /* the spreader evaluates tau itself; no point stream; each
                              lane takes a fixed run of consecutive samples */
@@ -145,7 +147,8 @@ typedef struct {
     int32_t parts;              /* waves per instance in the spreader: 1, 2, 4, 8 or 16
                                    (8 and 16 span 2 and 4 workgroups whose partial grids
                                    the epilogue adds); 0: automatic (more waves per
-                                   instance when the plan is too small to fill the GPU) */
+                                   instance when the plan is too small to fill the GPU,
+                                   for cell runs one for every 63 cells) */
     int32_t profile;            /* 1: time every kernel launch with HIP events */
     int32_t use_graph;          /* 1: capture each call's launches in a HIP graph, keyed by
                                    its pointer arguments, and replay it on later calls with
