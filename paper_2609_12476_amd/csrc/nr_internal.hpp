@@ -174,7 +174,7 @@ struct FilterItem {
     int64_t src_off;    // first sample of the segment in the caller's strain
     int64_t z_off;      // node values of the first frequency ([16 tiles][nodes])
     int64_t tap_off;    // carriers of the first tile: per tile [4 ksteps][64 lanes] (cosine, -sine) pairs
-    int64_t win_off;    // window [16 ksteps][images of k, padded to four]
+    int64_t win_off;    // window [16 ksteps][images of k, padded to four], k downwards as the carriers
     int32_t L;          // samples
     int32_t D;          // samples between nodes
     int32_t Q;          // period of the carriers in samples

@@ -582,9 +582,10 @@ int node_width(int fp64, int w)
 
 // Attenuation of the filter in dB and its half-width in nodes (Kaiser's
 // estimate of the length of a window for that attenuation and transition).
-// FP32: 150 dB, 3e-8, half the rounding of one FP32 value.  FP64 of width 12:
-// 218 dB, 1.2e-11 under a kernel error of 3.3e-11.
-double node_attenuation(int fp64, int node_w) { return !fp64 ? 150.0 : node_w == 12 ? 218.0 : 270.0; }
+// FP32: 158 dB, 1.3e-8, a fifth of the rounding of one FP32 value; the most that
+// the half-width for 150 dB allows.  FP64 of width 12: 218 dB, 1.2e-11 under a
+// kernel error of 3.3e-11.
+double node_attenuation(int fp64, int node_w) { return !fp64 ? 158.0 : node_w == 12 ? 218.0 : 270.0; }
 // Images of the filter's window on one period of the carriers (odd).
 int node_images(int fp64, int node_w) { return !fp64 ? 5 : node_w == 12 ? 7 : 9; }
 int node_half(int fp64, int node_w)
@@ -999,7 +1000,7 @@ bool plan_nodes(nr_plan_s& P)
             it.nodes = NB;
             it.j0 = -(half - 1) * D;
             // the window's images k + Q i of folded sample k (k = 0 and Q / 2 are
-            // met from both sides: halved)
+            // met from both sides: halved), the largest k first
             it.win_off = (int64_t)window[f].size();
             const std::vector<long double> h = node_filter_taps(D, half, node_attenuation(f, sh.node_w));
             window[f].resize(window[f].size() + (size_t)ksteps * 16 * stride, 0.0L);
@@ -1007,7 +1008,7 @@ bool plan_nodes(nr_plan_s& P)
                 for (int i = 0; i < images; ++i) {
                     const int d = std::abs(k + Q * (i - images / 2));
                     if (d < half * D)
-                        window[f][(size_t)it.win_off + (size_t)k * stride + i] = (k == 0 || 2 * k == Q ? 0.5L : 1.0L) * h[d];
+                        window[f][(size_t)it.win_off + (size_t)(ksteps * 16 - 1 - k) * stride + i] = (k == 0 || 2 * k == Q ? 0.5L : 1.0L) * h[d];
                 }
             const int64_t tap0 = (int64_t)carriers[f].size() / 2;
             const std::vector<long double> root = roots_of_unity(Q, -1);
@@ -1018,7 +1019,8 @@ bool plan_nodes(nr_plan_s& P)
                                    2 * (r % kFilterRows);
                 for (int k = 0; k <= Q / 2; ++k) {
                     const int at = (int)((int64_t)ref * k % Q);
-                    long double* q = row + (size_t)(k / 4) * 128 + (k & 3) * 32;
+                    const int slot = ksteps * 16 - 1 - k;
+                    long double* q = row + (size_t)(slot / 4) * 128 + (slot & 3) * 32;
                     q[0] = root[2 * at];
                     q[1] = root[2 * at + 1];
                 }
