@@ -573,19 +573,24 @@ constexpr double kNodeMinRate = 1.0 / (0.5 * (1.0 - kNodeTransition) - 0.5 / kNo
 // none.  The path's own error lies far below the tolerance, so where it
 // changes an instance's result it is by the sample path's kernel error: FP32
 // classes of w >= 6 (error 1.6e-5 and less) and FP64 classes of w >= 11
-// (3.1e-10) take it, looser ones keep their values.
+// (3.1e-10) take it, looser ones keep their values.  FP64 classes of w = 12 take
+// the nodes of width 14: on nodes of their own width the filter's error came on
+// top of the kernel's (1e-10: 2.0e-11 by samples, 2.15e-11 so, 5 bins 4.0e-12
+// and 1.04e-11; 5e-13 and 2.5e-13 at width 14).  32 masses x 60 segments: 171
+// us, 146 on nodes of width 12.
 int node_width(int fp64, int w)
 {
     if (!fp64) return w >= 6 && w <= 8 ? 8 : 0;
-    return w >= 11 && w <= 12 ? 12 : w > 12 && w <= 14 ? 14 : 0;
+    return w == 11 ? 12 : w >= 12 && w <= 14 ? 14 : 0;
 }
 
 // Attenuation of the filter in dB and its half-width in nodes (Kaiser's
 // estimate of the length of a window for that attenuation and transition).
 // FP32: 158 dB, 1.3e-8, a fifth of the rounding of one FP32 value; the most that
-// the half-width for 150 dB allows.  FP64 of width 12: 218 dB, 1.2e-11 under a
-// kernel error of 3.3e-11.
-double node_attenuation(int fp64, int node_w) { return !fp64 ? 158.0 : node_w == 12 ? 218.0 : 270.0; }
+// the half-width for 150 dB allows.  FP64 of width 12: 218 dB, 1.2e-11 under the
+// kernel error of 3.1e-10 of the classes of width 11; of width 14: 279 dB,
+// 1.1e-14 under 4.0e-13.
+double node_attenuation(int fp64, int node_w) { return !fp64 ? 158.0 : node_w == 12 ? 218.0 : 279.0; }
 // Images of the filter's window on one period of the carriers (odd).
 int node_images(int fp64, int node_w) { return !fp64 ? 5 : node_w == 12 ? 7 : 9; }
 int node_half(int fp64, int node_w)

@@ -43,3 +43,16 @@ def test_fp32_nodes_err_no_more_than_samples(gpu, name):
     nodes, samples = _rms_errors(gpu, name, "fp32", 1e-6)
     print(f"  nodes {nodes:.2e}, samples {samples:.2e}", flush=True)
     assert nodes <= samples
+
+
+# the loosest and the tightest class that samples spread with width 12, on small
+# grids and past them
+@pytest.mark.parametrize("name", ["search", "few_bins", "one_bin", "first_fft_grid"])
+@pytest.mark.parametrize("tol", [6e-10, 7e-11])
+def test_fp64_width_12_errs_no_more_than_samples(gpu, name, tol):
+    import paper_2609_12476_amd.nufft_resample as nr
+    print(f"node errors fp64 {name} {tol}", flush=True)
+    assert nr.nufft_resample_kernel_params(tol, 2.0, "fp64", 30).w == 12
+    nodes, samples = _rms_errors(gpu, name, "fp64", tol)
+    print(f"  nodes {nodes:.2e}, samples {samples:.2e}", flush=True)
+    assert nodes <= samples
