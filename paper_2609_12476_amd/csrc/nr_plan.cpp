@@ -1230,47 +1230,47 @@ bool build_plan(nr_plan_s& P, bool nodes, bool records, const nr_segment* segs, 
         NodePick pick{};
         double y_ext = 0.0;
         if (node_w && !pick_nodes(h, g, t, df_i, fp64, node_w, &pick, &y_ext)) node_w = 0;
-        double phase_steps = 0.0;   // heterodyne phase span in phase-table steps
+        // The heterodyne phase fc dtau is evaluated in FP64: the tau
+        // series (or log1p/expm1) and the product with fc each add a few
+        // units in the last place, so the phase in cycles carries a
+        // relative error of about (degree + 3) 2^-53, which grows with
+        // the cycles the segment spans.  An instance whose phase error
+        // would exceed a quarter of its tolerance cannot reach it in any
+        // precision class: an error in strict plans (otherwise the
+        // phase error bounds what the instance attains).  The phase must
+        // also stay below 2^38 cycles, far inside the range of the
+        // kernels' FP64 rounding to the nearest cycle or table step.
+        const long double span = h.beta == 0.0 ? h.c * (long double)(g.n_samples - 1)
+                                                : h.a * (1.0L - powl(1.0L - (long double)h.y_max, 0.625L));
+        const double fc = t.f_lo + (double)(K / 2) * df_i;
+        const double cycles = std::fabs(fc) * (double)span;
+        const double phase_steps = cycles * (double)phase_table_size(fp64);   // its span in phase-table steps
+        if (cycles * 1024.0 >= 281474976710656.0)
+            fail(NR_ERR_INVALID_ARG, "instance " + std::to_string(i) +
+                                         ": heterodyne frequency x duration too large (over 2^38 cycles)");
+        const auto phase_error = [&](int deg) {
+            return 2.0 * M_PI * cycles * ((deg > 0 ? deg : deg == 0 ? 1 : 8) + 3.0) * 0x1p-53;
+        };
         if (h.beta != 0.0) {
             const double f_ref = std::fabs(t.f_lo) + (double)K * df_i + df_i;
             if (node_w) {
+                // the nodes reach past the segment: a longer series, which in a
+                // strict plan may be too coarse where the samples' is not
                 InstHost he = h;
                 he.y_max = y_ext;
                 ndeg = horner_series(he, f_ref, fp64 ? 1e-14 : 1e-11, series);
-                if (ndeg < 0) {
+                if (ndeg < 0 || (o.strict && phase_error(ndeg) > 0.25 * tol_eff)) {
                     node_w = 0;
                     series.clear();
                 }
             }
             if (!node_w) ndeg = horner_series(h, f_ref, fp64 ? 1e-14 : 1e-11, series);
         }
-        {
-            // The heterodyne phase fc dtau is evaluated in FP64: the tau
-            // series (or log1p/expm1) and the product with fc each add a few
-            // units in the last place, so the phase in cycles carries a
-            // relative error of about (degree + 3) 2^-53, which grows with
-            // the cycles the segment spans.  An instance whose phase error
-            // would exceed a quarter of its tolerance cannot reach it in any
-            // precision class: an error in strict plans (otherwise the
-            // phase error bounds what the instance attains).  The phase must
-            // also stay below 2^38 cycles, far inside the range of the
-            // kernels' FP64 rounding to the nearest cycle or table step.
-            const long double span = h.beta == 0.0 ? h.c * (long double)(g.n_samples - 1)
-                                                    : h.a * (1.0L - powl(1.0L - (long double)h.y_max, 0.625L));
-            const double fc = t.f_lo + (double)(K / 2) * df_i;
-            const double cycles = std::fabs(fc) * (double)span;
-            phase_steps = cycles * (double)phase_table_size(fp64);
-            if (cycles * 1024.0 >= 281474976710656.0)
-                fail(NR_ERR_INVALID_ARG, "instance " + std::to_string(i) +
-                                             ": heterodyne frequency x duration too large (over 2^38 cycles)");
-            const double terms = (ndeg > 0 ? ndeg : ndeg == 0 ? 1 : 8) + 3;
-            const double phase_err = 2.0 * M_PI * cycles * terms * 0x1p-53;
-            if (o.strict && phase_err > 0.25 * tol_eff)
-                fail(NR_ERR_TOL_UNATTAINABLE,
-                     "instance " + std::to_string(i) + ": the FP64 heterodyne phase over " +
-                         std::to_string(cycles) + " cycles is accurate to about " + std::to_string(phase_err) +
-                         " rad, too coarse for tolerance " + std::to_string(tol_eff));
-        }
+        if (o.strict && phase_error(ndeg) > 0.25 * tol_eff)
+            fail(NR_ERR_TOL_UNATTAINABLE,
+                 "instance " + std::to_string(i) + ": the FP64 heterodyne phase over " + std::to_string(cycles) +
+                     " cycles is accurate to about " + std::to_string(phase_error(ndeg)) +
+                     " rad, too coarse for tolerance " + std::to_string(tol_eff));
         int method = resolve_method(o.method);
         if (node_w) method = NR_METHOD_CELLRUN;
         // records need every class in one chunk; a plan of kLargePlanWaves or

@@ -1,0 +1,97 @@
+// Checks of the plan code's choices on a recording HIP runtime (fake_hip.hpp):
+// one check per name, picked by the first argument.  Exit status 0 if it holds.
+#include "fake_hip.hpp"
+
+#include <cmath>
+#include <cstdio>
+
+#include "nufft_resample.h"
+
+namespace {
+
+struct Bank {
+    std::vector<nr_segment> segs;
+    std::vector<nr_template> tmpls;
+};
+
+// n_seg segments of L samples at fs; n_mc chirp masses x n_sub sub-bands of K bins of df from 40 Hz on
+Bank bank(int n_seg, int64_t L, double fs, int n_mc, int n_sub, int K, double df, double mc0 = 1e-3, double mc1 = 1e-1)
+{
+    Bank b;
+    for (int i = 0; i < n_seg; ++i) b.segs.push_back({i * L, L, fs, (double)(i * L) / fs});
+    for (int m = 0; m < n_mc; ++m)
+        for (int s = 0; s < n_sub; ++s) {
+            nr_template t{};
+            t.mc_msun = mc0 * std::pow(mc1 / mc0, n_mc > 1 ? m / (n_mc - 1.0) : 0.0);
+            t.f_lo = 40.0 + s;
+            t.f0 = t.f_lo + 0.5 * K * df;
+            t.df = df;
+            t.n_bins = K;
+            b.tmpls.push_back(t);
+        }
+    return b;
+}
+
+nr_status plan(nr_plan* p, const Bank& b, double tol, const nr_options& o)
+{
+    return nufft_resample_plan(p, b.segs.data(), (int)b.segs.size(), b.tmpls.data(), (int)b.tmpls.size(), nullptr, 0,
+                               tol, &o);
+}
+
+nr_options options(int precision)
+{
+    nr_options o;
+    nufft_resample_default_options(&o);
+    o.precision = precision;
+    return o;
+}
+
+bool has_nodes(nr_plan p)
+{
+    nr_plan_info info;
+    nufft_resample_query(p, &info);
+    for (int c = 0; c < info.n_classes; ++c) {
+        nr_node_info n;
+        nufft_resample_query_nodes(p, c, &n);
+        if (n.width) return true;
+    }
+    return false;
+}
+
+// A strict plan accepts the tolerances that it accepts on the samples: the node
+// path's tau series spans more than the segment and may be longer.
+int strict()
+{
+    int refused = 0, with_nodes = 0, accepted = 0;
+    for (double mc1 : {2e-2, 5e-2, 1e-1})
+        for (double tol = 1e-11; tol < 2e-10; tol *= 1.02) {
+            const Bank b = bank(2, 7680, 256.0, 24, 2, 30, 1.0 / 30, 1e-2, mc1);
+            nr_options o = options(NR_FP64);
+            o.strict = 1;
+            nr_plan p = nullptr, q = nullptr;
+            const nr_status a = plan(&p, b, tol, o);
+            o.method = NR_METHOD_CELLRUN;
+            const nr_status s = plan(&q, b, tol, o);
+            if (a != s) {
+                std::printf("mc %g tol %g: status %d, %d on samples (%s)\n", mc1, tol, (int)a, (int)s,
+                            nufft_resample_last_error(nullptr));
+                ++refused;
+            }
+            if (s == NR_OK) ++accepted;
+            if (a == NR_OK && has_nodes(p)) ++with_nodes;
+            nufft_resample_destroy(p);
+            nufft_resample_destroy(q);
+        }
+    std::printf("%d accepted on samples, %d with nodes, %d differ\n", accepted, with_nodes, refused);
+    return refused || !accepted || !with_nodes;
+}
+
+}  // namespace
+
+int main(int argc, char** argv)
+{
+    const std::string name = argc > 1 ? argv[1] : "";
+    if (name == "strict") return strict();
+    std::printf("no check of that name\n");
+    return 2;
+}
