@@ -85,6 +85,7 @@ struct DevBuf {
         hipError_t e = hipMalloc(&p, b);
         if (e != hipSuccess) {
             p = nullptr;
+            (void)hipGetLastError();   // reported here: the next launch's check must not find it
             fail(NR_ERR_OUT_OF_MEMORY, std::string("device allocation of ") + std::to_string(b) +
                                            " bytes for " + what + " failed: " + hipGetErrorString(e));
         }

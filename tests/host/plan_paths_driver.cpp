@@ -86,12 +86,47 @@ int strict()
     return refused || !accepted || !with_nodes;
 }
 
+// Whichever allocation of the node path fails, the plan is built on the samples
+// and its calls do not meet the allocation's error again.
+int fallback()
+{
+    const Bank b = bank(2, 7680, 256.0, 24, 2, 30, 1.0 / 30);
+    const nr_options o = options(NR_FP32);
+    nr_plan p = nullptr;
+    int64_t before = fake_hip::allocations;
+    if (plan(&p, b, 1e-6, o) != NR_OK || !has_nodes(p)) return 1;
+    const int64_t n = fake_hip::allocations - before;
+    nufft_resample_destroy(p);
+    std::vector<float> strain(2 * 7680), stat(48 * 30), power(48 * 2 * 30);
+    int bad = 0, samples = 0;
+    for (int64_t k = 0; k < n; ++k) {
+        fake_hip::fail_at = fake_hip::allocations + k;
+        const nr_status st = plan(&p, b, 1e-6, o);
+        fake_hip::fail_at = -1;
+        const nr_status e = st != NR_OK ? st : nufft_resample_execute(p, strain.data(), nullptr, power.data(), nullptr);
+        const nr_status u =
+            st != NR_OK ? st : nufft_resample_semicoherent_sum(p, strain.data(), nullptr, stat.data(), nullptr);
+        if (st != NR_OK || e != NR_OK || u != NR_OK) {
+            std::printf("allocation %d: plan %d, execute %d, sum %d: %s\n", (int)k, (int)st, (int)e, (int)u,
+                        st != NR_OK ? nufft_resample_last_error(nullptr) : nufft_resample_last_error(p));
+            ++bad;
+        } else if (!has_nodes(p)) {
+            ++samples;
+        }
+        nufft_resample_destroy(p);
+        (void)hipGetLastError();
+    }
+    std::printf("%d allocations, %d fall back, %d bad\n", (int)n, samples, bad);
+    return bad || samples != n;
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "strict") return strict();
+    if (name == "fallback") return fallback();
     std::printf("no check of that name\n");
     return 2;
 }
