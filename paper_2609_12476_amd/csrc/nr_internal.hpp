@@ -208,7 +208,9 @@ struct NodeArgs {
     int32_t im_off;          // small grids: first imaginary part after the first real part
 };
 
-// LDS of a large-grid workgroup: the grid, and four strips or the FFT's other half.
+// LDS of a large-grid workgroup: the grid, and four strips or the FFT's other
+// half; the strips' first cells lie in static LDS beside them.
+constexpr size_t kNodeFftStaticLds = 4 * sizeof(int);
 inline size_t node_fft_lds_bytes(int fp64, int n, int strip)
 {
     return (size_t)(n + (4 * strip > n ? 4 * strip : n)) * (fp64 ? 16 : 8);

@@ -638,6 +638,7 @@ __global__ __launch_bounds__(kBlock) void node_spread_fft_kernel(NodeArgs a, Epi
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ int bases[4];
+    static_assert(sizeof(bases) == kNodeFftStaticLds, "counted by the plan");
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
     const int wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n = a.n, len = a.strip;

@@ -1077,7 +1077,8 @@ bool plan_nodes(nr_plan_s& P)
     // round the grid many times: the sample path
     if (worst > 1.0) return false;
     for (auto& cp : P.classes)
-        if (cp->node_w && node_lds_bytes(*cp) > (cp->n <= kNodeDftMax ? kLdsBytes / 2 : kLdsBytes)) return false;
+        if (cp->node_w && node_lds_bytes(*cp) > (cp->n <= kNodeDftMax ? kLdsBytes / 2 : kLdsBytes - kNodeFftStaticLds))
+            return false;
     const int64_t cap = P.opt.max_workspace_bytes > 0 ? P.opt.max_workspace_bytes : (int64_t(8) << 30);
     if (z[0] * 8 + z[1] * 16 > cap) return false;
     for (int f = 0; f < 2; ++f) {

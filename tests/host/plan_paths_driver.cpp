@@ -120,6 +120,35 @@ int fallback()
     return bad || samples != n;
 }
 
+// A large grid whose strips would fill the LDS to the last byte leaves the
+// kernel's 16 static bytes no room: the plan takes the samples.  Bins ever
+// further apart pass that size (n = 240 and four strips of 5060 cells).
+int full_lds()
+{
+    int met = 0, over = 0, below = 0;
+    std::vector<float> strain(491520), power(64 * 120);
+    for (double df = 2.80; df < 2.8060 && !over; df += 2e-5) {
+        Bank b = bank(1, 491520, 16384.0, 64, 1, 120, df);
+        for (nr_template& t : b.tmpls) t.mc_msun = 0.0;
+        nr_plan p = nullptr;
+        if (plan(&p, b, 1e-6, options(NR_FP32)) != NR_OK) return 1;
+        fake_hip::launches.clear();
+        if (nufft_resample_execute(p, strain.data(), nullptr, power.data(), nullptr) != NR_OK) return 1;
+        bool fft = false;
+        for (const fake_hip::Launch& l : fake_hip::launches)
+            if (l.is("node_spread_fft")) {
+                fft = true;
+                over += l.lds + 16 > 160 * 1024;
+                below += l.lds > 160 * 1024 - 256;
+                std::printf("df %.5f lds %zu\n", df, l.lds);
+            }
+        met += !fft;
+        nufft_resample_destroy(p);
+    }
+    std::printf("%d plans just below, %d on samples, %d over\n", below, met, over);
+    return over || !below || !met;
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -127,6 +156,7 @@ int main(int argc, char** argv)
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "strict") return strict();
     if (name == "fallback") return fallback();
+    if (name == "full_lds") return full_lds();
     std::printf("no check of that name\n");
     return 2;
 }
