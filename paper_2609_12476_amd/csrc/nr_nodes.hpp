@@ -24,6 +24,8 @@
 //                  the Stockham FFT for large grids), deconvolution, power.
 #pragma once
 
+#include <algorithm>
+
 #include "nr_fft.hpp"
 #include "nr_internal.hpp"
 
@@ -679,6 +681,9 @@ __global__ __launch_bounds__(kBlock) void node_spread_fft_kernel(NodeArgs a, Epi
 
 // -------------------------------------------------------------- launches --
 
+// Workgroups of one launch at most: a launch holds fewer than 2^32 threads.
+constexpr int64_t kMostBlocks = int64_t(1) << 23;
+
 size_t filter_lds_bytes(int fp64, int D, int Q, int ksteps, int images)
 {
     const int kp = 16 * ksteps, reach = images / 2 * Q + kp;
@@ -689,8 +694,10 @@ template <typename T, typename Ti, int I, int MAXT>
 static hipError_t launch_node_filter_k(const FilterLaunch& f, const void* strain, void* z, hipStream_t st)
 {
     allow_lds(node_filter_kernel<T, Ti, I, MAXT>, f.lds);
-    node_filter_kernel<T, Ti, I, MAXT><<<dim3((unsigned)f.count), dim3(kBlock), f.lds, st>>>(
-        f.items, (const Ti*)strain, (const T*)f.carriers, (const T*)f.window, (cpx<T>*)z);
+    for (int64_t at = 0; at < f.count; at += kMostBlocks)
+        node_filter_kernel<T, Ti, I, MAXT>
+            <<<dim3((unsigned)std::min(f.count - at, kMostBlocks)), dim3(kBlock), f.lds, st>>>(
+                f.items + at, (const Ti*)strain, (const T*)f.carriers, (const T*)f.window, (cpx<T>*)z);
     return hipGetLastError();
 }
 
@@ -719,15 +726,17 @@ hipError_t launch_node_filter(const FilterLaunch& f, const void* strain, void* z
 template <typename T, int W, int NE>
 static hipError_t launch_node_spread_k(const NodeArgs& a, const EpilogueOut& o, hipStream_t st)
 {
-    if (a.mtiles > 0) {
-        const size_t lds = (size_t)kNodeBatch * a.gstride * sizeof(T);
-        allow_lds(node_spread_dft_kernel<T, W, NE>, lds);
-        node_spread_dft_kernel<T, W, NE>
-            <<<dim3((unsigned)((a.count + kNodeBatch - 1) / kNodeBatch)), dim3(kBlock), lds, st>>>(a, o);
-    } else {
-        const size_t lds = node_fft_lds_bytes(sizeof(T) == 8, a.n, a.strip);
-        allow_lds(node_spread_fft_kernel<T, W, NE>, lds);
-        node_spread_fft_kernel<T, W, NE><<<dim3((unsigned)a.count), dim3(kBlock), lds, st>>>(a, o);
+    const bool small = a.mtiles > 0;
+    const size_t lds = small ? (size_t)kNodeBatch * a.gstride * sizeof(T)
+                             : node_fft_lds_bytes(sizeof(T) == 8, a.n, a.strip);
+    const int64_t per = small ? kNodeBatch : 1;      // instances of a workgroup
+    auto* kernel = small ? node_spread_dft_kernel<T, W, NE> : node_spread_fft_kernel<T, W, NE>;
+    allow_lds(kernel, lds);
+    for (int64_t at = 0; at < a.count; at += kMostBlocks * per) {
+        NodeArgs q = a;
+        q.inst = a.inst + at;
+        q.count = std::min(a.count - at, kMostBlocks * per);
+        kernel<<<dim3((unsigned)((q.count + per - 1) / per)), dim3(kBlock), lds, st>>>(q, o);
     }
     return hipGetLastError();
 }

@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdio>
 
+#include "nr_internal.hpp"
 #include "nufft_resample.h"
 
 namespace {
@@ -149,6 +150,53 @@ int full_lds()
     return over || !below || !met;
 }
 
+// The launches of more node instances, or filter work, than one launch's 2^32
+// threads hold are split, each piece with its own records.
+int large_launches()
+{
+    fake_hip::arg_bytes = sizeof(nr::NodeArgs);
+    nr::NodeArgs a{};
+    a.inst = reinterpret_cast<const nr::InstDev*>(uintptr_t(1) << 40);   // (never read here)
+    a.count = (int64_t(1) << 24) + 5;
+    a.n = 144;
+    a.w = 8;
+    a.strip = 40;
+    int bad = 0;
+    for (const int small : {0, 1}) {
+        a.mtiles = small ? 4 : 0;
+        a.count = (small ? int64_t(1) << 28 : int64_t(1) << 24) + 5;
+        fake_hip::launches.clear();
+        bad += nr::launch_node_spread(a, 0, nr::EpilogueOut{}, nullptr) != hipSuccess;
+        int64_t at = 0;
+        for (const fake_hip::Launch& l : fake_hip::launches) {
+            nr::NodeArgs q;
+            std::memcpy(&q, l.arg.data(), sizeof q);
+            bad += q.inst != a.inst + at || (int64_t)l.grid.x * (small ? nr::kNodeBatch : 1) < q.count;
+            at += q.count;
+        }
+        bad += at != a.count;
+    }
+    nr::FilterLaunch f{};
+    f.items = reinterpret_cast<const nr::FilterItem*>(uintptr_t(1) << 40);
+    f.count = (int64_t(1) << 24) + 5;
+    f.tiles = 1;
+    f.images = 5;
+    f.lds = 60000;
+    fake_hip::launches.clear();
+    fake_hip::arg_bytes = sizeof(f.items);
+    bad += nr::launch_node_filter(f, nullptr, nullptr, 0, 0, nullptr) != hipSuccess;
+    int64_t at = 0;
+    for (const fake_hip::Launch& l : fake_hip::launches) {
+        const nr::FilterItem* items;
+        std::memcpy(&items, l.arg.data(), sizeof items);
+        bad += items != f.items + at;
+        at += l.grid.x;
+    }
+    bad += at != f.count;
+    std::printf("%d bad\n", bad);
+    return bad;
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -157,6 +205,7 @@ int main(int argc, char** argv)
     if (name == "strict") return strict();
     if (name == "fallback") return fallback();
     if (name == "full_lds") return full_lds();
+    if (name == "large_launches") return large_launches();
     std::printf("no check of that name\n");
     return 2;
 }
