@@ -227,6 +227,7 @@ struct nr_plan_s {
     std::string err;
     nr_options opt{};
     int radix_override = 0;           // autotuner mini-plans: radix_code of every class
+    bool mini = false;                // autotuner mini-plans: laid out as the tuned plan is, without records
     hipStream_t stream = nullptr;
     int32_t n_segs = 0, n_tmpls = 0;
     int64_t n_inst = 0;
@@ -1644,7 +1645,7 @@ bool nodes_allowed(const nr_options& o, int radix_override)
 void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_template* tmpls,
                  int32_t n_tmpls, const nr_instance* inst, int64_t n_inst, double tol)
 {
-    const bool nodes = nodes_allowed(P.opt, P.radix_override), records = records_allowed(P.opt);
+    const bool nodes = nodes_allowed(P.opt, P.radix_override), records = records_allowed(P.opt) && !P.mini;
     for (int level = 0; level < 2; ++level) {
         if (!(level ? records : nodes)) continue;
         try {
@@ -2243,6 +2244,7 @@ double time_config(const nr_options& base, const nr_segment& g, const nr_templat
     std::vector<nr_instance> il((size_t)batch, nr_instance{0, 0, tol});
     nr_plan_s mini;
     mini.opt = o2;
+    mini.mini = true;
     create_plan(mini, &s1, 1, &t, 1, il.data(), batch, tol);
     semicoherent(mini, strain, nullptr, stat, used);  // warm-up
     hipEvent_t a, b;
@@ -2292,6 +2294,7 @@ double time_fft_plan(const nr_options& base, const nr_segment& g, const nr_templ
     std::vector<nr_instance> il((size_t)batch, nr_instance{0, 0, tol});
     nr_plan_s mini;
     mini.opt = o2;
+    mini.mini = true;
     mini.radix_override = radix;
     create_plan(mini, &s1, 1, &t, 1, il.data(), batch, tol);
     semicoherent(mini, strain, nullptr, stat, used);  // warm-up

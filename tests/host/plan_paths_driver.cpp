@@ -4,6 +4,7 @@
 
 #include <cmath>
 #include <cstdio>
+#include <tuple>
 
 #include "nr_internal.hpp"
 #include "nufft_resample.h"
@@ -197,6 +198,51 @@ int large_launches()
     return bad;
 }
 
+// What the tuner times is what the tuned plan runs: with cell runs made the
+// cheapest, the plan's spread launch (grid, LDS, waves an instance, records) is
+// among those of the mini-plans.
+int tuner()
+{
+    fake_hip::arg_bytes = sizeof(nr::SpreadArgs);
+    fake_hip::cost = [](const fake_hip::Launch& l) {
+        return l.is("spread_runs") ? 0.1 : l.is("spread") || l.is("tau") ? 10.0 : 0.1;
+    };
+    int bad = 0;
+    // (a shape's choice is kept for the process: a length of its own for each)
+    int64_t L = 7680;
+    for (const int precision : {NR_FP32, NR_FP64, NR_AUTO})
+        for (const int n : {1, 16, 300}) {
+            L += 4;
+            Bank b = bank(n, L, 256.0, 1, 1, 600, 1.0 / 30);
+            nr_options o = options(precision);
+            o.tune = 1;
+            fake_hip::launches.clear();
+            nr_plan p = nullptr;
+            if (plan(&p, b, precision == NR_FP64 ? 1e-9 : 1e-6, o) != NR_OK) return 1;
+            const std::vector<fake_hip::Launch> timed = fake_hip::launches;
+            std::vector<double> strain(n * L), power(n * 600);
+            fake_hip::launches.clear();
+            if (nufft_resample_execute(p, strain.data(), nullptr, power.data(), nullptr) != NR_OK) return 1;
+            int runs = 0;
+            for (const fake_hip::Launch& l : fake_hip::launches)
+                if (l.is("spread_runs")) {
+                    const auto shape = [](const fake_hip::Launch& q) {
+                        nr::SpreadArgs a;
+                        std::memcpy(&a, q.arg.data(), sizeof a);
+                        return std::make_tuple(q.kernel, q.grid.x, q.lds, a.count, a.n, a.parts, a.rec_stride, a.rec_shift);
+                    };
+                    bool found = false;
+                    for (const fake_hip::Launch& q : timed) found = found || (q.is("spread_runs") && shape(q) == shape(l));
+                    bad += !found;
+                    ++runs;
+                }
+            std::printf("precision %d, %d instances: %d cell-run launches, %d bad so far\n", precision, n, runs, bad);
+            if (!runs) return 1;
+            nufft_resample_destroy(p);
+        }
+    return bad;
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -206,6 +252,7 @@ int main(int argc, char** argv)
     if (name == "fallback") return fallback();
     if (name == "full_lds") return full_lds();
     if (name == "large_launches") return large_launches();
+    if (name == "tuner") return tuner();
     std::printf("no check of that name\n");
     return 2;
 }
