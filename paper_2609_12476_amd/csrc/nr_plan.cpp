@@ -215,6 +215,7 @@ struct Group {
     int fp64 = 0, deg = 0, fused = 1, snap = 0;
     int fuse_epi = 0;                  // epilogue groups: classes whose spreader writes the outputs
     size_t lds[2] = {0, 0};            // spread: [0]; epilogue: [0] spectra, [1] segment sum
+    bool mixed = false;                // spread: classes of different LDS tiers, all resident at once
     double cost = 0.0;                 // spread: relative duration
     int64_t blocks[2] = {0, 0};
     SpreadTable spread{};              // class tables (kernel arguments)
@@ -1808,8 +1809,8 @@ void build_groups(nr_plan_s& P)
             const Group& g = P.spread_groups[q];
             // node classes are launched one by one
             if (c.node_w || g.cls.size() >= (size_t)kGroupMax) continue;
-            if (lds_tier(sl) == lds_tier(g.lds[0]) ||
-                g.blocks[0] + blocks <= (int64_t)kCus * lds_tier(std::max(sl, g.lds[0]))) {
+            const bool same = !g.mixed && lds_tier(sl) == lds_tier(g.lds[0]);
+            if (same || g.blocks[0] + blocks <= (int64_t)kCus * lds_tier(std::max(sl, g.lds[0]))) {
                 at = q;
                 break;
             }
@@ -1825,6 +1826,7 @@ void build_groups(nr_plan_s& P)
             g.snap = snap;
         }
         Group& g = P.spread_groups[at];
+        if (!g.cls.empty()) g.mixed = g.mixed || lds_tier(sl) != lds_tier(g.lds[0]);
         g.blocks[0] += blocks;
         g.cls.push_back((int)ci);
         // a launch lasts as long as one lane's samples take (a step of a sample

@@ -2,6 +2,7 @@
 // one check per name, picked by the first argument.  Exit status 0 if it holds.
 #include "fake_hip.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <tuple>
@@ -243,6 +244,58 @@ int tuner()
     return bad;
 }
 
+// A merged launch takes a class below the occupancy that its own LDS allows only
+// if every workgroup of the launch is resident at once.
+int groups()
+{
+    fake_hip::arg_bytes = sizeof(nr::SpreadTable);
+    const auto tier = [](size_t lds) { return (int64_t)std::min<size_t>(8, 160 * 1024 / std::max<size_t>(lds, 1)); };
+    int bad = 0, merged = 0, lowered = 0;
+    // templates of 30 bins (2 KB of LDS), of 1200 (77 KB) and of 1250 (80 KB) in every order
+    const int K[3] = {30, 1200, 1250};
+    const int orders[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
+    for (const auto& order : orders)
+        for (int many = 0; many < 4; ++many) {           // which of them has 4096 (3: none)
+            Bank b = bank(1, 7680, 256.0, 1, 1, 30, 1.0 / 30);
+            const nr_template t = b.tmpls[0];
+            b.tmpls.clear();
+            for (const int k : order)
+                for (int q = 0; q < (k == many ? 4096 : 8); ++q) {
+                    b.tmpls.push_back(t);
+                    b.tmpls.back().n_bins = K[k];
+                }
+            nr_options o = options(NR_FP32);
+            o.method = NR_METHOD_FUSED;
+            o.parts = 1;
+            nr_plan p = nullptr;
+            if (plan(&p, b, 1e-6, o) != NR_OK) return 1;
+            std::vector<float> strain(7680);
+            float power = 0.0f;                          // (launches write nothing here)
+            fake_hip::launches.clear();
+            if (nufft_resample_execute(p, strain.data(), nullptr, &power, nullptr) != NR_OK) return 1;
+            for (const fake_hip::Launch& l : fake_hip::launches) {
+                if (!l.is("spread") || !l.is("SpreadTable")) continue;
+                nr::SpreadTable tab;
+                std::memcpy(&tab, l.arg.data(), sizeof tab);
+                ++merged;
+                for (int c = 0; c < tab.ncls; ++c) {
+                    const nr::SpreadArgs& a = tab.a[c];
+                    const size_t own = nr::spread_lds_bytes(0, a.n, a.epi_fused && a.parts == 1);
+                    if (tier(own) <= tier(l.lds)) continue;
+                    ++lowered;
+                    if (l.grid.x > 256 * tier(l.lds)) {
+                        std::printf("order %d %d %d, many %d: %u workgroups of %zu bytes hold a class of %zu\n", order[0],
+                                    order[1], order[2], many, l.grid.x, l.lds, own);
+                        ++bad;
+                    }
+                }
+            }
+            nufft_resample_destroy(p);
+        }
+    std::printf("%d merged launches, %d classes below their occupancy, %d wrongly\n", merged, lowered, bad);
+    return bad || !merged || !lowered;
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -253,6 +306,7 @@ int main(int argc, char** argv)
     if (name == "full_lds") return full_lds();
     if (name == "large_launches") return large_launches();
     if (name == "tuner") return tuner();
+    if (name == "groups") return groups();
     std::printf("no check of that name\n");
     return 2;
 }
