@@ -229,9 +229,11 @@ hipError_t launch_node_filter(const FilterLaunch& f, const void* strain, void* z
                               hipStream_t st);
 
 // Launch wrappers (defined in nr_kernels.hip).
-// max_entries: the largest parts * C * 64 of the segments (sizes the grid).
-hipError_t launch_strain_lane_major(const SegDev* segs, int32_t n_segs, int64_t max_entries, const void* strain,
-                                    int strain_fp64, int strain_complex, int dst_fp64, hipStream_t st);
+// max_entries: the largest parts * C * 64 of the segments (sizes the grid);
+// plain: every copy keeps the order of the samples (C = 1).
+hipError_t launch_strain_lane_major(const SegDev* segs, int32_t n_segs, int64_t max_entries, int plain,
+                                    const void* strain, int strain_fp64, int strain_complex, int dst_fp64,
+                                    hipStream_t st);
 // One launch over up to kGroupMax classes of the same kernel instantiation:
 // their arguments travel in the kernel arguments (so that the kernel knows
 // every pointer in them addresses global memory), block_off[c] is the first

@@ -22,6 +22,7 @@
 // sum_j c_j exp(-2 pi i m df dtau_j) = X(f_c + m df).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <cstdint>
 #include <type_traits>
@@ -1465,14 +1466,31 @@ size_t epilogue_lds_bytes(int fp64, int n, int K_max, int sum_mode)
     return b;
 }
 
-hipError_t launch_strain_lane_major(const SegDev* segs, int32_t n_segs, int64_t max_entries, const void* strain,
-                                    int strain_fp64, int strain_complex, int dst_fp64, hipStream_t st)
+// Workgroups a segment of the strain copies: kCopyAhead entries per thread of
+// the largest segment, at most 64; lane-major copies of short segments 16 entries
+// in launches that fill the GPU either way (2048 segments of 7680 FP32 samples: 53
+// us so, 72 with four entries; 512 of complex ones: 14.9 and 17.3; 128: 8.9 and
+// 6.6), until the source passes the last-level cache (4096 of double to float: 186
+// and 169).  Segments of 30720 want four in any large launch (512: 70 and 46;
+// 128: 13.9 and 15.1).
+static int64_t copy_blocks(int64_t n_segs, int64_t max_entries, int entry_bytes, bool plain)
+{
+    const auto blocks = [&](int per) {
+        const int64_t g = (max_entries + kBlock * per - 1) / (kBlock * per);
+        return std::max<int64_t>(1, std::min<int64_t>(64, g));
+    };
+    const int64_t most = blocks(kCopyAhead);
+    if (plain || n_segs * most <= 1024) return most;
+    const bool large = max_entries > 16384 || n_segs * max_entries * entry_bytes > 200000000;
+    return large && n_segs * most > 4096 ? most : blocks(16);
+}
+
+hipError_t launch_strain_lane_major(const SegDev* segs, int32_t n_segs, int64_t max_entries, int plain,
+                                    const void* strain, int strain_fp64, int strain_complex, int dst_fp64,
+                                    hipStream_t st)
 {
     if (n_segs <= 0) return hipSuccess;
-    // kCopyAhead entries per thread of the largest segment, at most 64 workgroups per segment
-    int64_t gy = (max_entries + kBlock * kCopyAhead - 1) / (kBlock * kCopyAhead);
-    if (gy < 1) gy = 1;
-    if (gy > 64) gy = 64;
+    const int64_t gy = copy_blocks(n_segs, max_entries, (strain_fp64 ? 8 : 4) * (strain_complex ? 2 : 1), plain);
     dim3 grid((unsigned)n_segs, (unsigned)gy), block(kBlock);
     if (strain_fp64 && dst_fp64)
         strain_lane_major_kernel<double, double><<<grid, block, 0, st>>>(segs, (const double*)strain, strain_complex);

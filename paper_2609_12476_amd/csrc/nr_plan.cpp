@@ -244,6 +244,7 @@ struct nr_plan_s {
     // lane-major layout of every class, by destination precision
     std::vector<SegDev> lm_segs[2];
     int64_t lm_max_entries[2] = {0, 0};
+    int lm_plain[2] = {1, 1};          // every copy of the precision has C = 1
     DevBuf d_lm_segs[2];
     // batched mode: every class in one chunk with its own grid region, the
     // classes launched in groups instead of one after another
@@ -1532,6 +1533,7 @@ bool build_plan(nr_plan_s& P, bool nodes, bool records, const nr_segment* segs, 
             sd.dst = c.d_strain.p;
             P.lm_segs[c.fp64].push_back(sd);
             P.lm_max_entries[c.fp64] = std::max(P.lm_max_entries[c.fp64], (int64_t)sd.parts * sd.C * kWave);
+            if (sd.C != 1) P.lm_plain[c.fp64] = 0;
         }
         c.d_tmpl_id.upload(c.tmpl_id, "templates");
         c.d_tmpl_list.upload(c.tmpl_list, "template lists");
@@ -1942,7 +1944,8 @@ void lane_major(nr_plan_s& P, const void* strain)
         if (!P.lm_segs[f].empty())
             timed_launch(P, NR_STAGE_LAYOUT, [&] {
                 return launch_strain_lane_major((const SegDev*)P.d_lm_segs[f].p, (int32_t)P.lm_segs[f].size(),
-                                                P.lm_max_entries[f], strain, P.strain_fp64, P.opt.strain_complex,
+                                                P.lm_max_entries[f], P.lm_plain[f], strain, P.strain_fp64,
+                                                P.opt.strain_complex,
                                                 f, P.stream);
             }, "strain layout");
     for (int f = 0; f < 2; ++f)

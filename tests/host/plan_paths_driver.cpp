@@ -296,6 +296,41 @@ int groups()
     return bad || !merged || !lowered;
 }
 
+// Workgroups a segment of the lane-major strain copies: few entries a thread where
+// compute units would idle or the strain passes the last-level cache, else more.
+int copies()
+{
+    const struct {
+        int n;
+        int64_t L;
+        double fs;
+        int precision;
+        unsigned y;
+    } want[] = {{1, 7680, 256.0, NR_FP32, 8},       {128, 7680, 256.0, NR_FP32, 8},    {512, 7680, 256.0, NR_FP32, 2},
+                {2048, 7680, 256.0, NR_FP32, 2},    {4096, 7680, 256.0, NR_AUTO, 8},   {2048, 1920, 64.0, NR_FP64, 1},
+                {128, 30720, 1024.0, NR_FP32, 8},   {512, 30720, 1024.0, NR_FP32, 30}};
+    int bad = 0;
+    for (const auto& c : want) {
+        Bank b = bank(c.n, c.L, c.fs, 1, 1, 30, 1.0 / 30);
+        nr_options o = options(c.precision);
+        o.method = NR_METHOD_FUSED;
+        o.parts = 1;
+        nr_plan p = nullptr;
+        if (plan(&p, b, c.precision == NR_FP64 ? 1e-9 : 1e-6, o) != NR_OK) return 1;
+        std::vector<double> strain(1);
+        float power = 0.0f;
+        fake_hip::launches.clear();
+        if (nufft_resample_execute(p, strain.data(), nullptr, &power, nullptr) != NR_OK) return 1;
+        for (const fake_hip::Launch& l : fake_hip::launches)
+            if (l.is("strain_lane_major") && (l.grid.x != (unsigned)c.n || l.grid.y != c.y)) {
+                std::printf("%d segments of %d: %u x %u\n", c.n, (int)c.L, l.grid.x, l.grid.y);
+                ++bad;
+            }
+        nufft_resample_destroy(p);
+    }
+    return bad;
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -307,6 +342,7 @@ int main(int argc, char** argv)
     if (name == "large_launches") return large_launches();
     if (name == "tuner") return tuner();
     if (name == "groups") return groups();
+    if (name == "copies") return copies();
     std::printf("no check of that name\n");
     return 2;
 }
