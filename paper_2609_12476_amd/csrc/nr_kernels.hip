@@ -906,6 +906,11 @@ __device__ __forceinline__ void spread_runs_block(const SpreadArgs& a, const Epi
         const double inv_s0 = 1.0 / (dfn * (tc.ndeg > 0 ? tc.bc[0] : tc.c));
         const E* __restrict__ xs = reinterpret_cast<const E*>(a.strain_lm) + d.strain_off;
         const int last_quad = ((L + kWave - 1) & ~(kWave - 1)) - 4;   // of the segment's copy
+        // FP32 complex strain: long runs take aligned quads, of which none lies in
+        // two cache lines; in short ones the second masked quad costs more (51
+        // samples a cell, 512 instances: 61 us unaligned, 54 aligned; 13 a cell,
+        // 4096 instances: 183 and 200; in FP64 neither is faster at 51)
+        const bool aligned = CPLX && sizeof(T) == 4 && (double)L >= 24.0 * (U1 - U0 + 1.0);
         // leading series coefficient, kept in a vector register
         double top = tc.ndeg > 0 ? tc.b[tc.ndeg - 1] : 0.0;
         asm volatile("" : "+v"(top));
@@ -938,11 +943,19 @@ __device__ __forceinline__ void spread_runs_block(const SpreadArgs& a, const Epi
             Moments<T, D> M;
             M.zero();
             // quads from the run's first sample on, wherever it lies (16-byte
-            // loads need no more than the element's alignment); the last one is
-            // masked (samples outside the run enter with zero strength) and
-            // moved back where it would pass the copy's padding
+            // loads need no more than the element's alignment), or from the
+            // aligned one before it ('aligned', above); the last one is masked
+            // (samples outside the run enter with zero strength) and moved back
+            // where it would pass the copy's padding
             int q = js;
             double jq = (double)js;
+            if (aligned && je > js) {
+                q = js & ~3;
+                jq = (double)q;
+                cell_quad<T, D, CPLX, true>(tc, top, xs, q, jq, js, je, dfn, hnn, u1, fcs, tab, M);
+                q += 4;
+                jq += 4.0;
+            }
             for (; q + 4 <= je; q += 4, jq += 4.0)
                 cell_quad<T, D, CPLX, false>(tc, top, xs, q, jq, q, je, dfn, hnn, u1, fcs, tab, M);
             if (q < je) {
