@@ -32,12 +32,41 @@ __device__ __forceinline__ double lane_value(double v, int k)
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// PER fold slots a thread, r = r0 + p 256 + threadIdx.x of segment blockIdx.y:
-// the grid points r, r + fold, ... < M of each, in that order.
+// One thread per fold slot r of segment blockIdx.y: the grid points r,
+// r + fold, ... < M, in that order.
+template <bool CPLX>
+__global__ __launch_bounds__(256) void plain_fold_kernel(const float* __restrict__ x, int64_t n, double fs_o, double a,
+                                                         double tscale, int identity, int64_t M, int64_t fold,
+                                                         float2* __restrict__ out)
+{
+#pragma clang fp contract(off)
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= fold) return;
+    x += (int64_t)blockIdx.y * n * (CPLX ? 2 : 1);
+    out += (int64_t)blockIdx.y * fold;
+    float re = 0.0f, im = 0.0f;
+    for (int64_t m = r; m < M; m += fold) {
+        const double tau = (double)m / fs_o;
+        const double t = identity ? tau : -expm1(1.6 * log1p(-tau / a)) * tscale;
+        const double q = rint(t * fs_o);
+        if (q >= 0.0 && q < (double)n) {
+            const int64_t s = (int64_t)q;
+            if (CPLX) {
+                re += x[2 * s];
+                im += x[2 * s + 1];
+            } else {
+                re += x[s];
+            }
+        }
+    }
+    out[r] = make_float2(re, im);
+}
+
+// The same for kSlots fold slots a thread, r = r0 + p 256 + threadIdx.x.
 //
 // The sample nearest to a grid point is rint of the inverse time map, whose
-// log1p and expm1 in FP64 bound the kernel (8 segments of 2^20 samples, a
-// million grid points each: 52 us; now 24).  The points of one workgroup and one
+// log1p and expm1 in FP64 bound the kernel above (8 segments of 2^20 samples, a
+// million grid points each: 52 us; 21 so).  The points of one workgroup and one
 // multiple of the fold lie close together, so one evaluation in their middle
 // (lane k does that for multiple k) serves them all: with z = d / (fs a y),
 // d the distance in points and y = 1 - tau / a in the middle, the map is
@@ -49,42 +78,39 @@ __device__ __forceinline__ double lane_value(double v, int k)
 // about ten operations of 2^-53 each).  Elsewhere, about two points in a
 // million, and where the series is not short enough, the plain evaluation
 // decides.
-template <bool CPLX, int PER>
+constexpr int kSlots = 8;
+template <bool CPLX>
 __global__ __launch_bounds__(256) void fold_kernel(const float* __restrict__ x, int64_t n, double fs_o, double a,
-                                                   double tscale, int identity, int64_t M, int64_t fold,
-                                                   float2* __restrict__ out)
+                                                   double tscale, int64_t M, int64_t fold, float2* __restrict__ out)
 {
 #pragma clang fp contract(off)
-    const int64_t r0 = (int64_t)blockIdx.x * (256 * PER);
+    const int64_t r0 = (int64_t)blockIdx.x * (256 * kSlots);
     x += (int64_t)blockIdx.y * n * (CPLX ? 2 : 1);
     out += (int64_t)blockIdx.y * fold;
-    constexpr double kHalf = 128.0 * PER;
+    constexpr double kHalf = 128.0 * kSlots;
     const int lane = threadIdx.x & 63;
     const double A = tscale * fs_o;
-    float re[PER], im[PER];
+    float re[kSlots], im[kSlots];
 #pragma unroll
-    for (int p = 0; p < PER; ++p) re[p] = im[p] = 0.0f;
+    for (int p = 0; p < kSlots; ++p) re[p] = im[p] = 0.0f;
     for (int64_t m0 = r0; m0 < M; m0 += 64 * fold) {
         const double xm = ((double)(m0 + lane * fold) + kHalf) / fs_o / a;
         const double E = expm1(1.6 * log1p(-xm));        // y^1.6 - 1
         const double G = A * (1.0 + E), z1 = 1.0 / (fs_o * a * (1.0 - xm)), zm = kHalf * z1;
-        const bool near = !identity && zm > 0.0 && zm < 0.1 && 0.02 * G * zm * zm * zm * zm * zm < 1e-7;
+        const bool near = zm > 0.0 && zm < 0.1 && 0.02 * G * zm * zm * zm * zm * zm < 1e-7;
         const double mine = near ? z1 : NAN, Qm = -E * A;   // NAN: no comparison below holds
         for (int k = 0; k < 64 && m0 + k * fold < M; ++k) {
             const double zs = lane_value(mine, k), Q = lane_value(Qm, k), g = lane_value(G, k);
 #pragma unroll
-            for (int p = 0; p < PER; ++p) {
+            for (int p = 0; p < kSlots; ++p) {
                 const int at = p * 256 + threadIdx.x;
                 const int64_t m = m0 + k * fold + at;
                 if (r0 + at >= fold || m >= M) continue;
                 const double z = ((double)at - kHalf) * zs;
                 const double v = fma(g, z * fma(z, -fma(z, fma(z, 0.0224, 0.064), 0.48), 1.6), Q);
                 double q = rint(v);
-                if (!(fabs(v - q) < 0.5 - 1e-6 - 1e-14 * fabs(v))) {
-                    const double tau = (double)m / fs_o;
-                    const double t = identity ? tau : -expm1(1.6 * log1p(-tau / a)) * tscale;
-                    q = rint(t * fs_o);
-                }
+                if (!(fabs(v - q) < 0.5 - 1e-6 - 1e-14 * fabs(v)))
+                    q = rint(-expm1(1.6 * log1p(-((double)m / fs_o) / a)) * tscale * fs_o);
                 if (q >= 0.0 && q < (double)n) {
                     const int64_t s = (int64_t)q;
                     if (CPLX) {
@@ -98,15 +124,17 @@ __global__ __launch_bounds__(256) void fold_kernel(const float* __restrict__ x, 
         }
     }
 #pragma unroll
-    for (int p = 0; p < PER; ++p) {
+    for (int p = 0; p < kSlots; ++p) {
         const int64_t r = r0 + p * 256 + threadIdx.x;
         if (r < fold) out[r] = make_float2(re[p], im[p]);
     }
 }
 
-// Slots a thread: eight, to share one evaluation among 2048 points, where that
-// leaves two workgroups a compute unit.
-constexpr int kSlots = 8;
+// Shared evaluations where eight slots a thread leave two workgroups a compute
+// unit; below that, with one slot a thread, the series' one load at a time takes
+// longer than the evaluations that it spares (1 x 2^20 samples on 2^18 slots 9.6
+// us plain, 12.3 with the series; 8 x 2^18 on 2^16 16.9 and 22.3).  The identity
+// has none to spare (8 x 2^20 samples: 14.8 us, 25.0).
 constexpr int64_t kManyBlocks = 512;
 
 template <bool CPLX>
@@ -114,11 +142,10 @@ void launch_fold(const float* x, int64_t n, int32_t n_seg, double fs_o, double a
                  int64_t M, int64_t fold, float2* out, hipStream_t st)
 {
     const int64_t many = (fold + 256 * kSlots - 1) / (256 * kSlots);
-    if (many * n_seg >= kManyBlocks)
-        fold_kernel<CPLX, kSlots><<<dim3((unsigned)many, (unsigned)n_seg), 256, 0, st>>>(x, n, fs_o, a, tscale,
-                                                                                       identity, M, fold, out);
+    if (!identity && many * n_seg >= kManyBlocks)
+        fold_kernel<CPLX><<<dim3((unsigned)many, (unsigned)n_seg), 256, 0, st>>>(x, n, fs_o, a, tscale, M, fold, out);
     else
-        fold_kernel<CPLX, 1><<<dim3((unsigned)((fold + 255) / 256), (unsigned)n_seg), 256, 0, st>>>(
+        plain_fold_kernel<CPLX><<<dim3((unsigned)((fold + 255) / 256), (unsigned)n_seg), 256, 0, st>>>(
             x, n, fs_o, a, tscale, identity, M, fold, out);
 }
 
