@@ -191,9 +191,11 @@ nr_status nr_prop_topk(const float* scores, int64_t rows, int32_t n, int32_t k, 
     // ranking costs n^2 comparisons a row over the whole GPU, the sort one
     // workgroup a row: below this line ranking takes less (64 rows of
     // 500 scores 8.5 against 10.7 us, 32 of 1000 10.4 against 14.4, 2 of 16384
-    // 94 against 148; above it 64 of 1000 take 19.0 against 14.6)
+    // 94 against 148; above it 64 of 1000 take 19.0 against 14.6).  Rows of up to
+    // four scores are sorted in one to three passes (8192 of one score 13.6 us,
+    // ranked 21.0; 8192 of four 19.8 and 21.0; 4096 of five 15.5 and 11.5)
     const int64_t nb = (n + kRankItems - 1) / kRankItems;
-    if (rows * n <= 32768) {
+    if (n > 4 && rows * n <= 32768) {
         const size_t lds = (size_t)((n + kRankParts - 1) / kRankParts) * kRankParts * sizeof(uint64_t);
         if (lds > 60000) {
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(topk_rank_kernel),

@@ -36,3 +36,17 @@ def test_fold_on_both_sides_of_the_line(gpu, n, fs, mc, fold, n_seg, cplx):
     idx = ost.nearest(t, fs, n)
     for i in (0, 1, n_seg // 2, n_seg - 1):
         assert np.array_equal(got[i], _fold(x[i], idx, fold).astype(np.complex64)), i
+
+
+# rows of one to four scores are sorted, of five and more ranked
+@pytest.mark.parametrize("rows,n,k", [(1, 1, 1), (4097, 1, 1), (8192, 4, 4), (6553, 5, 3), (5, 4, 2), (5, 5, 5)])
+def test_topk_of_short_rows(gpu, rows, n, k):
+    import torch
+    from paper_2609_12476_amd import proposal as pp
+    print(f"topk short rows={rows} n={n} k={k}", flush=True)
+    rng = np.random.default_rng(rows + n)
+    s = np.round(rng.standard_normal((rows, n)) * 2).astype(np.float32)
+    s[::7, 0] = np.nan
+    s[::5, n - 1] = -np.inf
+    got = pp.nr_prop_topk(torch.from_numpy(s).to(gpu), rows, n, k).cpu().numpy()
+    assert np.array_equal(got, op.topk(s.astype(np.float64), k))
