@@ -86,8 +86,8 @@ struct Mfma<double> {
 // workgroup and node spacings of 4 (mod 8), whose reads met on half the banks,
 // 35 us with up to four tiles, 29 us free of bank conflicts (the latency of
 // 11 us of matrix steps at two waves a SIMD); beta bank 31 -> 20 us.
-template <typename T, typename Ti, int MT, int I>
-__device__ __forceinline__ void node_filter_block(const FilterItem& it, const Ti* __restrict__ strain,
+template <typename T, int MT, int I>
+__device__ __forceinline__ void node_filter_block(const FilterItem& it, const T* __restrict__ strain,
                                                   const T* __restrict__ carriers, const T* __restrict__ window,
                                                   cpx<T>* __restrict__ z, T* __restrict__ lds)
 {
@@ -99,18 +99,18 @@ __device__ __forceinline__ void node_filter_block(const FilterItem& it, const Ti
     // window of the workgroup's nodes: sample w0 is xs[0]
     const int64_t w0 = (int64_t)it.j0 + (int64_t)it.node0 * D - reach;
     const int len = (kNodeTile - 1) * D + 2 * reach + 1;
-    const Ti* __restrict__ src = strain + it.src_off;
+    const T* __restrict__ src = strain + it.src_off;
     // 16 loads in flight per thread
     for (int q0 = threadIdx.x; q0 < len; q0 += 16 * kBlock) {
-        Ti v[16];
+        T v[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             const int64_t j = w0 + q0 + u * kBlock;
-            v[u] = q0 + u * kBlock < len && j >= 0 && j < it.L ? src[j] : Ti(0);
+            v[u] = q0 + u * kBlock < len && j >= 0 && j < it.L ? src[j] : T(0);
         }
 #pragma unroll
         for (int u = 0; u < 16; ++u)
-            if (q0 + u * kBlock < len) xs[q0 + u * kBlock] = (T)v[u];
+            if (q0 + u * kBlock < len) xs[q0 + u * kBlock] = v[u];
     }
     for (int q0 = threadIdx.x; q0 < kp * IS; q0 += 8 * kBlock) {
         T v[8];
@@ -195,9 +195,9 @@ __device__ __forceinline__ void node_filter_block(const FilterItem& it, const Ti
 
 // MAXT: the most tiles of any item of the launch (its registers set the
 // kernel's occupancy: 16 accumulators a tile in FP32).
-template <typename T, typename Ti, int I, int MAXT>
+template <typename T, int I, int MAXT>
 __global__ __launch_bounds__(kBlock) void node_filter_kernel(const FilterItem* __restrict__ items,
-                                                             const Ti* __restrict__ strain,
+                                                             const T* __restrict__ strain,
                                                              const T* __restrict__ carriers,
                                                              const T* __restrict__ window, cpx<T>* __restrict__ z)
 {
@@ -206,13 +206,13 @@ __global__ __launch_bounds__(kBlock) void node_filter_kernel(const FilterItem* _
     const FilterItem it = items[blockIdx.x];
     const int tiles = uniform(it.tiles);
     if (MAXT == 1 || tiles == 1)
-        node_filter_block<T, Ti, 1, I>(it, strain, carriers, window, z, lds);
+        node_filter_block<T, 1, I>(it, strain, carriers, window, z, lds);
     else if (MAXT == 2 || tiles == 2)
-        node_filter_block<T, Ti, 2, I>(it, strain, carriers, window, z, lds);
+        node_filter_block<T, 2, I>(it, strain, carriers, window, z, lds);
     else if (tiles == 3)
-        node_filter_block<T, Ti, 3, I>(it, strain, carriers, window, z, lds);
+        node_filter_block<T, 3, I>(it, strain, carriers, window, z, lds);
     else
-        node_filter_block<T, Ti, 4, I>(it, strain, carriers, window, z, lds);
+        node_filter_block<T, 4, I>(it, strain, carriers, window, z, lds);
 }
 
 // ---------------------------------------------------------------- spread --
@@ -492,27 +492,18 @@ __device__ __forceinline__ int node_strip(const InstDev& d, const NodeArgs& a, c
     return base + 1;      // tap 0 of S lands on cell floor(S) + 1
 }
 
-// The outputs of bin k of an instance, as the fused epilogue writes them:
-// power rows (mode 1) or spectra and power at the bin offsets (mode 2).
+// The outputs of bin k of an instance, as the fused epilogue writes them (of the
+// class's own type: FP32 node classes have FP32 outputs): power rows (mode 1) or
+// spectra and power at the bin offsets (mode 2).
 template <typename T>
 __device__ __forceinline__ void node_store(const NodeArgs& a, const EpilogueOut& o, const InstDev& d, int k, cpx<T> X)
 {
-    if (o.out_fp64) {
-        const double pw = (double)X.x * (double)X.x + (double)X.y * (double)X.y;
-        if (o.mode == 1) {
-            reinterpret_cast<double*>(o.rows)[a.row_base + (int64_t)d.entry * a.kmax + k] = pw;
-        } else {
-            if (o.spectra) reinterpret_cast<cpx<double>*>(o.spectra)[d.bin_off + k] = cpx<double>{(double)X.x, (double)X.y};
-            if (o.power) reinterpret_cast<double*>(o.power)[d.bin_off + k] = pw;
-        }
+    const T pw = X.x * X.x + X.y * X.y;
+    if (o.mode == 1) {
+        reinterpret_cast<T*>(o.rows)[a.row_base + (int64_t)d.entry * a.kmax + k] = pw;
     } else {
-        const float pw = (float)X.x * (float)X.x + (float)X.y * (float)X.y;
-        if (o.mode == 1) {
-            reinterpret_cast<float*>(o.rows)[a.row_base + (int64_t)d.entry * a.kmax + k] = pw;
-        } else {
-            if (o.spectra) reinterpret_cast<cpx<float>*>(o.spectra)[d.bin_off + k] = cpx<float>{(float)X.x, (float)X.y};
-            if (o.power) reinterpret_cast<float*>(o.power)[d.bin_off + k] = pw;
-        }
+        if (o.spectra) reinterpret_cast<cpx<T>*>(o.spectra)[d.bin_off + k] = X;
+        if (o.power) reinterpret_cast<T*>(o.power)[d.bin_off + k] = pw;
     }
 }
 
@@ -690,23 +681,23 @@ size_t filter_lds_bytes(int fp64, int D, int Q, int ksteps, int images)
     return (size_t)((kNodeTile - 1) * D + 2 * reach + 1 + kp * ((images + 3) / 4 * 4)) * (fp64 ? 8 : 4);
 }
 
-template <typename T, typename Ti, int I, int MAXT>
+template <typename T, int I, int MAXT>
 static hipError_t launch_node_filter_k(const FilterLaunch& f, const void* strain, void* z, hipStream_t st)
 {
-    allow_lds(node_filter_kernel<T, Ti, I, MAXT>, f.lds);
+    allow_lds(node_filter_kernel<T, I, MAXT>, f.lds);
     for (int64_t at = 0; at < f.count; at += kMostBlocks)
-        node_filter_kernel<T, Ti, I, MAXT>
+        node_filter_kernel<T, I, MAXT>
             <<<dim3((unsigned)std::min(f.count - at, kMostBlocks)), dim3(kBlock), f.lds, st>>>(
-                f.items + at, (const Ti*)strain, (const T*)f.carriers, (const T*)f.window, (cpx<T>*)z);
+                f.items + at, (const T*)strain, (const T*)f.carriers, (const T*)f.window, (cpx<T>*)z);
     return hipGetLastError();
 }
 
-template <typename T, typename Ti, int I>
+template <typename T, int I>
 static hipError_t launch_node_filter_t(const FilterLaunch& f, const void* strain, void* z, hipStream_t st)
 {
-    if (f.tiles == 1) return launch_node_filter_k<T, Ti, I, 1>(f, strain, z, st);
-    if (f.tiles == 2 || filter_tiles(sizeof(T) == 8) == 2) return launch_node_filter_k<T, Ti, I, 2>(f, strain, z, st);
-    if constexpr (filter_tiles(sizeof(T) == 8) == 4) return launch_node_filter_k<T, Ti, I, 4>(f, strain, z, st);
+    if (f.tiles == 1) return launch_node_filter_k<T, I, 1>(f, strain, z, st);
+    if (f.tiles == 2 || filter_tiles(sizeof(T) == 8) == 2) return launch_node_filter_k<T, I, 2>(f, strain, z, st);
+    if constexpr (filter_tiles(sizeof(T) == 8) == 4) return launch_node_filter_k<T, I, 4>(f, strain, z, st);
     return hipErrorInvalidValue;
 }
 
@@ -714,13 +705,13 @@ hipError_t launch_node_filter(const FilterLaunch& f, const void* strain, void* z
                               hipStream_t st)
 {
     if (f.count <= 0) return hipSuccess;
+    // (FP32 classes over double strain read samples: the strain has the nodes' type)
+    if (strain_fp64 != fp64) return hipErrorInvalidValue;
     if (fp64)
-        return f.images == 7 ? launch_node_filter_t<double, double, 7>(f, strain, z, st)
-               : f.images == 9 ? launch_node_filter_t<double, double, 9>(f, strain, z, st)
+        return f.images == 7 ? launch_node_filter_t<double, 7>(f, strain, z, st)
+               : f.images == 9 ? launch_node_filter_t<double, 9>(f, strain, z, st)
                                : hipErrorInvalidValue;
-    if (f.images != 5) return hipErrorInvalidValue;
-    if (strain_fp64) return launch_node_filter_t<float, double, 5>(f, strain, z, st);
-    return launch_node_filter_t<float, float, 5>(f, strain, z, st);
+    return f.images == 5 ? launch_node_filter_t<float, 5>(f, strain, z, st) : hipErrorInvalidValue;
 }
 
 template <typename T, int W, int NE>
