@@ -331,6 +331,55 @@ int copies()
     return bad;
 }
 
+// Which of the shapes that the GPU tests of records plan take them: all but the
+// segment of three samples, whose cells hold fewer than 1.5 each.
+int records()
+{
+    fake_hip::arg_bytes = sizeof(nr::SpreadArgs);
+    const struct {
+        int n;
+        int64_t L;
+        double fs;
+        int K;
+        double df;      // <= 0: 1 / T
+        bool rec;
+    } shapes[] = {{1, 3, 256.0, 1, 0.0, false},      {3, 65, 256.0, 16, 0.0, true},
+                  {2, 7681, 256.0, 600, 0.0, true},  {5, 2560, 256.0, 200, 0.0, true},
+                  {4, 7679, 256.0, 32, 8 / 30., true}, {2, 30719, 1024.0, 40, 0.0, true},
+                  {130, 4099, 128.0, 130, 1 / 16., true}, {700, 1025, 128.0, 140, 1 / 8., true},
+                  {1, 3, 256.0, 2, 1e-3, false},     {1, 4, 256.0, 2, 1e-3, true},
+                  {1, 5, 256.0, 2, 1e-3, true},      {1, 7, 256.0, 2, 1e-3, true},
+                  {1, 63, 256.0, 2, 1e-3, true},     {1, 64, 256.0, 2, 1e-3, true}};
+    int bad = 0;
+    for (const auto& q : shapes)
+        for (const double tol : {1e-3, 1e-6, 1e-9, 1e-12}) {
+            Bank b = bank(2, q.L, q.fs, q.n, 1, q.K, q.df, 1e-4, 1e-3);
+            for (nr_template& t : b.tmpls) t.f0 = t.f_lo = 100.0;
+            nr_options o = options(tol < 1e-6 ? NR_FP64 : NR_FP32);
+            o.method = NR_METHOD_CELLRUN;
+            nr_plan p = nullptr;
+            if (plan(&p, b, tol, o) != NR_OK) return 1;
+            std::vector<double> strain(1);
+            double power = 0.0;
+            fake_hip::launches.clear();
+            if (nufft_resample_execute(p, strain.data(), nullptr, &power, nullptr) != NR_OK) return 1;
+            bool any = false, all = true;
+            for (const fake_hip::Launch& l : fake_hip::launches)
+                if (l.is("spread_runs")) {
+                    nr::SpreadArgs a;
+                    std::memcpy(&a, l.arg.data(), sizeof a);
+                    any = true;
+                    all = all && (a.rec_stride > 0) == q.rec;
+                }
+            if (!any || !all) {
+                std::printf("%d x %d, %d bins, tol %g: not as expected\n", q.n, (int)q.L, q.K, tol);
+                ++bad;
+            }
+            nufft_resample_destroy(p);
+        }
+    return bad;
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -343,6 +392,7 @@ int main(int argc, char** argv)
     if (name == "tuner") return tuner();
     if (name == "groups") return groups();
     if (name == "copies") return copies();
+    if (name == "records") return records();
     std::printf("no check of that name\n");
     return 2;
 }
