@@ -162,7 +162,10 @@ typedef struct {
     int32_t tune;               /* 1: at plan creation, time the candidate spreader
                                    configurations (parts, flush period, fused or staged) of
                                    every shape (precision, kernel width, grid size, samples)
-                                   on a small synthetic batch and use the fastest */
+                                   on a small synthetic batch and use the fastest.  The
+                                   candidates read samples: a tuned plan takes no
+                                   band-limited nodes, with which a plan whose templates
+                                   share segments may be several times faster untuned */
     int32_t flush_period;       /* steps between collective flushes of the spreader (1..64,
                                    power of two); 0: chosen from the sample density */
     int32_t moment_mode;        /* spreader moments: 0 automatic, 1 restarted per grid cell,
@@ -220,8 +223,11 @@ typedef struct {
  * values instead of its samples: the segment, filtered to the few hertz around
  * a reference frequency at a rate of a few times that width, once for all
  * templates of that frequency.  The sum over the nodes equals the sum over the
- * samples to 3e-8 (FP32 classes) or 1e-11 (FP64), below the class's kernel
- * error.  Such a class reports method NR_METHOD_CELLRUN and parts 1.
+ * samples to 2e-8 (FP32 classes), 1e-11 (nodes of width 12) or 1e-14 (width 14),
+ * below the kernel error of the classes that take them: the spectra are no
+ * further from exact sums than those from samples.  In strict plans an instance
+ * whose nodes are too coarse for its tolerance keeps its samples.  Such a class
+ * reports method NR_METHOD_CELLRUN and parts 1.
  */
 typedef struct {
     int32_t width;       /* spreading width on the nodes; 0: the class reads samples, all else 0 */
