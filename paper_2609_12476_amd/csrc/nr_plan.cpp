@@ -228,6 +228,7 @@ struct nr_plan_s {
     std::string err;
     nr_options opt{};
     int radix_override = 0;           // autotuner mini-plans: radix_code of every class
+    bool has_records = false;         // some class stores its rounds in records
     bool mini = false;                // autotuner mini-plans: laid out as the tuned plan is, without records
     hipStream_t stream = nullptr;
     int32_t n_segs = 0, n_tmpls = 0;
@@ -610,6 +611,72 @@ int node_dft_half(int n) { return (n + 15) / 16 * 4; }
 int node_coefs(int node_w) { return node_w == 8 ? 4 : node_w == 12 ? 7 : 9; }
 int node_count(int64_t L, int D, int half) { return (int)((L - 1) / D) + 2 * half; }
 
+// VALU lane-operations of an instance's samples, of its nodes, and of the filter
+// of one segment for `tiles` tiles: per 64 nodes two products of 16 tiles x 64 x
+// Q / 2 at twice the VALU's rate in FP32, and the folding.
+double samples_cost_of(int fp64, int64_t L) { return (double)L * (fp64 ? 73.0 : 55.0); }
+double node_spread_cost(int fp64, int node_w, int64_t L, int s)
+{
+    const int nodes = node_count(L, node_spacing(fp64, s), node_half(fp64, node_w));
+    return (double)((nodes + kWave - 1) / kWave) * kWave * (fp64 ? 170.0 : 85.0);
+}
+double node_filter_cost(int fp64, int node_w, int64_t L, int s, int tiles)
+{
+    const int D = node_spacing(fp64, s), nodes = node_count(L, D, node_half(fp64, node_w));
+    return (double)((nodes + kNodeTile - 1) / kNodeTile) * kNodeTile * (0.5 * kNodeRefs * D + 8.0) *
+           (2.0 * tiles * kFilterRows * (fp64 ? 1.0 : 0.5) + 5.0 * node_images(fp64, node_w));
+}
+
+// Whether any segment could be worth filtering: plan_nodes charges every segment
+// that it filters at least one tile, so a plan whose segments all have fewer
+// templates than that takes (or none that the path serves) is planned on its
+// samples at once (100,000 FP32 instances of a segment each: 0.60 s with an
+// attempt at nodes, 0.36 without).
+bool nodes_worth(const nr_segment* segs, int32_t n_segs, int32_t n_tmpls, const nr_instance* inst, int64_t n_inst,
+                 double tol, const nr_options& o)
+{
+    constexpr int kKinds = 3;
+    const int fp64_of[kKinds] = {0, 1, 1}, width_of[kKinds] = {8, 12, 14};
+    const auto kind_of = [&](double t) {
+        const int fp64 = o.precision == NR_FP64 || (o.precision == NR_AUTO && t < kFp32MinTol);
+        if (!fp64 && o.precision != NR_FP32) return -1;        // FP32 classes behind FP64 outputs
+        const int w = node_width(fp64, kernel_width(std::max(t, fp64 ? kFp64MinTol : kFp32MinTol), 2.0));
+        for (int k = 0; k < kKinds; ++k)
+            if (fp64_of[k] == fp64 && width_of[k] == w) return k;
+        return -1;
+    };
+    std::vector<std::array<int64_t, kKinds>> count((size_t)n_segs, std::array<int64_t, kKinds>{});
+    double last = tol;
+    int kind = kind_of(tol);
+    if (!inst) {
+        if (kind < 0) return false;
+        for (auto& c : count) c[(size_t)kind] = n_tmpls;
+    } else {
+        for (int64_t i = 0; i < n_inst; ++i) {
+            const double t = inst[i].tol > 0.0 ? inst[i].tol : tol;
+            if (t != last) kind = kind_of(last = t);
+            if (kind >= 0) ++count[(size_t)inst[i].segment][(size_t)kind];
+        }
+    }
+    int64_t L = -1;
+    double most[kKinds] = {};    // templates that a segment may have without paying for a tile
+    for (int32_t g = 0; g < n_segs; ++g) {
+        if (segs[g].n_samples != L) {
+            L = segs[g].n_samples;
+            for (int k = 0; k < kKinds; ++k) {
+                const int f = fp64_of[k], w = width_of[k];
+                double filter = INFINITY;
+                for (int s = 0; s < kNodeSpacings; ++s) filter = std::min(filter, node_filter_cost(f, w, L, s, 1));
+                const double gain = 0.5 * samples_cost_of(f, L) - node_spread_cost(f, w, L, 0);
+                most[k] = gain > 0.0 ? 0.999 * filter / gain : INFINITY;
+            }
+        }
+        for (int k = 0; k < kKinds; ++k)
+            if ((double)count[(size_t)g][(size_t)k] >= most[k]) return true;
+    }
+    return false;
+}
+
 // Node choice of an instance: the coarsest spacing whose rate resolves its
 // local frequencies f dtau' over the span that its nodes cover (the segment
 // and the filter's half-width on either side); y_ext: the series variable at
@@ -900,20 +967,9 @@ bool plan_nodes(nr_plan_s& P)
         v.f_hi = std::max(v.f_hi, p.centre);
     });
     if (shapes.empty()) return false;
-    // lane-operations of one node round of an instance, and of the filter of
-    // one segment for `tiles` tiles
-    auto nodes_of = [](const Shape& sh, int s) {
-        return node_count(sh.L, node_spacing(sh.fp64, s), node_half(sh.fp64, sh.node_w));
-    };
-    auto spread_cost = [&](const Shape& sh, int s) {
-        return (double)((nodes_of(sh, s) + kWave - 1) / kWave) * kWave * (sh.fp64 ? 170.0 : 85.0);
-    };
-    // per 64 nodes: two products of 16 tiles x 64 x Q / 2 at twice the VALU's
-    // rate in FP32, and the folding
-    auto filter_cost = [&](const Shape& sh, int s, int tiles) {
-        const double chunks = (double)((nodes_of(sh, s) + kNodeTile - 1) / kNodeTile);
-        return chunks * kNodeTile * (0.5 * kNodeRefs * node_spacing(sh.fp64, s) + 8.0) *
-               (2.0 * tiles * kFilterRows * (sh.fp64 ? 1.0 : 0.5) + 5.0 * node_images(sh.fp64, sh.node_w));
+    auto spread_cost = [](const Shape& sh, int s) { return node_spread_cost(sh.fp64, sh.node_w, sh.L, s); };
+    auto filter_cost = [](const Shape& sh, int s, int tiles) {
+        return node_filter_cost(sh.fp64, sh.node_w, sh.L, s, tiles);
     };
     for (auto& kv : shapes) {
         const Shape& sh = kv.first;
@@ -970,7 +1026,7 @@ bool plan_nodes(nr_plan_s& P)
     each([&](Class& c, InstDev& d, NodePick& p, const Shape& sh, std::array<Use, kNodeSpacings>& u) {
         u[p.spacing].rank[ref_of(p, sh) - u[p.spacing].lo] = 0;
         // about 55 (73 in FP64) lane-operations a sample, 85 (170) a node
-        samples_cost += (double)d.L * (c.fp64 ? 73.0 : 55.0);
+        samples_cost += samples_cost_of(c.fp64, d.L);
         node_cost += spread_cost(sh, p.spacing);
     });
     for (auto& kv : shapes)
@@ -1104,6 +1160,7 @@ bool build_plan(nr_plan_s& P, bool nodes, bool records, const nr_segment* segs, 
 {
     const nr_options& o = P.opt;
     validate(segs, n_segs, tmpls, n_tmpls, inst, n_inst, tol, o);
+    if (nodes && !nodes_worth(segs, n_segs, n_tmpls, inst, n_inst, tol, o)) return false;
     const double sigma = o.sigma > 0.0 ? o.sigma : 2.0;
     P.stream = (hipStream_t)o.stream;
     P.n_segs = n_segs;
@@ -1396,7 +1453,7 @@ bool build_plan(nr_plan_s& P, bool nodes, bool records, const nr_segment* segs, 
         c.kmax = std::max(c.kmax, K);
         c.n_points += g.n_samples;
     }
-    if (nodes && !plan_nodes(P)) return false;
+    P.has_records = any_records;
     if (nodes && o.max_workspace_bytes > 0) {
         // a cap that has the sample path split its grids into chunks means
         // that: the node path would hold the values of every segment at once
@@ -1404,6 +1461,7 @@ bool build_plan(nr_plan_s& P, bool nodes, bool records, const nr_segment* segs, 
         for (auto& cp : P.classes) grids += (int64_t)cp->inst.size() * cp->n * (cp->fp64 ? 16 : 8);
         if (grids > o.max_workspace_bytes / 2) return false;
     }
+    if (nodes && !plan_nodes(P)) return false;
     for (auto& cp : P.classes) {
         Class& c = *cp;
         if (!c.rec_stride) continue;
@@ -1654,7 +1712,8 @@ void create_plan(nr_plan_s& P, const nr_segment* segs, int32_t n_segs, const nr_
         try {
             if (build_plan(P, level == 0, records, segs, n_segs, tmpls, n_tmpls, inst, n_inst, tol)) return;
         } catch (const NrError& e) {
-            if (e.code != NR_ERR_OUT_OF_MEMORY) throw;
+            // (without nodes and records the plan is the last attempt's)
+            if (e.code != NR_ERR_OUT_OF_MEMORY || (level == 1 && !P.has_records)) throw;
         }
         const nr_options o = P.opt;
         const int radix = P.radix_override;

@@ -3,6 +3,7 @@
 #include "fake_hip.hpp"
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <tuple>
@@ -380,6 +381,64 @@ int records()
     return bad;
 }
 
+// Planning a segment an instance, which nodes cannot serve, takes no longer than
+// with the method given: no attempt at nodes is made and thrown away.
+int plan_time()
+{
+    const int n = 30000;
+    Bank b = bank(n, 7680, 256.0, n, 1, 30, 1.0 / 30, 1e-4, 1e-2);
+    std::vector<nr_instance> inst;
+    for (int i = 0; i < n; ++i) {
+        inst.push_back({i, i, 0.0});
+        b.segs[i].t_start = 0.0;
+    }
+    double best[2] = {1e9, 1e9};
+    for (int rep = 0; rep < 7; ++rep)
+        for (const int m : {0, 1}) {
+            nr_options o = options(NR_FP32);
+            o.method = m ? NR_METHOD_CELLRUN : NR_METHOD_AUTO;
+            nr_plan p = nullptr;
+            const auto t0 = std::chrono::steady_clock::now();
+            if (nufft_resample_plan(&p, b.segs.data(), n, b.tmpls.data(), n, inst.data(), n, 1e-6, &o) != NR_OK) return 1;
+            best[m] = std::min(best[m], std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
+            if (has_nodes(p)) return 1;
+            nufft_resample_destroy(p);
+        }
+    std::printf("automatic %.3f s, cell runs %.3f s\n", best[0], best[1]);
+    return best[0] > 1.3 * best[1];
+}
+
+// Templates a segment needs before nodes are planned: both sides of the line.
+int worth()
+{
+    int bad = 0, first[3] = {0, 0, 0};
+    const int precision[3] = {NR_FP32, NR_FP64, NR_FP64};
+    const double tol[3] = {1e-6, 1e-9, 1e-11};
+    for (int k = 0; k < 3; ++k)
+        for (int n = 1; n <= 64 && !first[k]; ++n) {
+            const Bank b = bank(2, 7680, 256.0, n, 1, 30, 1.0 / 30, 1e-3, 2e-3);
+            nr_plan p = nullptr;
+            if (plan(&p, b, tol[k], options(precision[k])) != NR_OK) return 1;
+            if (has_nodes(p)) first[k] = n;
+            nufft_resample_destroy(p);
+            // one segment with as many templates as its nodes need is enough, the other has one
+            if (first[k]) {
+                std::vector<nr_instance> inst;
+                for (int i = 0; i < 8 * n; ++i) inst.push_back({0, i % n, 0.0});
+                inst.push_back({1, 0, 0.0});
+                nr_options o = options(precision[k]);
+                p = nullptr;
+                if (nufft_resample_plan(&p, b.segs.data(), 2, b.tmpls.data(), n, inst.data(), (int64_t)inst.size(), tol[k],
+                                        &o) != NR_OK)
+                    return 1;
+                bad += !has_nodes(p);
+                nufft_resample_destroy(p);
+            }
+        }
+    std::printf("nodes from %d, %d and %d templates a segment on, %d bad\n", first[0], first[1], first[2], bad);
+    return bad || !first[0] || !first[1] || !first[2] || first[0] < 2;
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -393,6 +452,8 @@ int main(int argc, char** argv)
     if (name == "groups") return groups();
     if (name == "copies") return copies();
     if (name == "records") return records();
+    if (name == "plan_time") return plan_time();
+    if (name == "worth") return worth();
     std::printf("no check of that name\n");
     return 2;
 }

@@ -26,7 +26,8 @@ def driver(tmp_path_factory):
     return str(exe)
 
 
-@pytest.mark.parametrize("check", ["strict", "fallback", "full_lds", "large_launches", "tuner", "groups", "copies", "records"])
+@pytest.mark.parametrize("check", ["strict", "fallback", "full_lds", "large_launches", "tuner", "groups", "copies",
+                                   "records", "plan_time", "worth"])
 def test_plan_paths(driver, check):
     r = subprocess.run([driver, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-4000:] + r.stderr[-2000:]
