@@ -1252,6 +1252,8 @@ bool build_plan(nr_plan_s& P, bool nodes, bool records, const nr_segment* segs, 
     ClassKey last_key{-1, -1, -1, -1, -1, -1, -1, -1, -1};
     std::vector<double> series;
     size_t last_ci = 0;
+    const int64_t cap = o.max_workspace_bytes > 0 ? o.max_workspace_bytes : (int64_t(8) << 30);
+    int64_t grids = 0, rows = 0;       // bytes of the instances so far
     for (int64_t i = 0; i < N; ++i) {
         const nr_segment& g = P.segs[P.inst_seg[i]];
         const nr_template& t = P.tmpls[P.inst_tmpl[i]];
@@ -1449,18 +1451,19 @@ bool build_plan(nr_plan_s& P, bool nodes, bool records, const nr_segment* segs, 
             c.coef.insert(c.coef.end(), series.begin(), series.end());
         }
         if (node_w) c.picks.push_back(pick);
+        if (nodes) {
+            // a cap that has the sample path split its grids into chunks means
+            // that: the node path would hold the values of every segment at once;
+            // and it writes every instance's power row before the sum
+            grids += (int64_t)n * (fp64 ? 16 : 8);
+            rows += (int64_t)K * (P.out_fp64 ? 8 : 4);
+            if ((o.max_workspace_bytes > 0 && grids > o.max_workspace_bytes / 2) || rows > cap) return false;
+        }
         c.inst.push_back(d);
         c.kmax = std::max(c.kmax, K);
         c.n_points += g.n_samples;
     }
     P.has_records = any_records;
-    if (nodes && o.max_workspace_bytes > 0) {
-        // a cap that has the sample path split its grids into chunks means
-        // that: the node path would hold the values of every segment at once
-        int64_t grids = 0;
-        for (auto& cp : P.classes) grids += (int64_t)cp->inst.size() * cp->n * (cp->fp64 ? 16 : 8);
-        if (grids > o.max_workspace_bytes / 2) return false;
-    }
     if (nodes && !plan_nodes(P)) return false;
     for (auto& cp : P.classes) {
         Class& c = *cp;
@@ -1473,7 +1476,6 @@ bool build_plan(nr_plan_s& P, bool nodes, bool records, const nr_segment* segs, 
     // Lane-major strain layout per class, point-stream offsets, templates
     const size_t psize_f = 8, psize_d = 16;
     int64_t grid_chunk_bytes = 0, point_chunk_bytes = 0, grid_total = 0, point_total = 0;
-    const int64_t cap = o.max_workspace_bytes > 0 ? o.max_workspace_bytes : (int64_t(8) << 30);
     int64_t fixed_bytes = (int64_t)(P.d_z[0].bytes + P.d_z[1].bytes);
     for (auto& cp : P.classes) {
         Class& c = *cp;
